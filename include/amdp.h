@@ -442,24 +442,26 @@ int amdp_device_copy(void* dst, const void* src, size_t bytes, void* hip_stream)
 /* Kernel-selection switches for tests and measurements; none changes what is
  * computed beyond rounding order inside a product. Takes effect from the next
  * call on.
- *   AMDP_OPT_GEMM_TILE               0 = the library's choice (default); 256, 128, 64 or
- *                                    BM*1000+BN (128064, 64128) force that matrix-core tile
- *                                    where it divides the product's shape; -1 = generic kernel
- *   AMDP_OPT_GEMM_TRANSPOSING_READS  1 (default) m/n-contiguous operands are read from LDS with
- *                                    the transposing read; 0 element by element
- *   AMDP_OPT_GEMM_DIRECT_TO_LDS      tiles loaded from global memory straight into LDS: 1 (default)
- *                                    where measured faster, 0 never, 2 wherever the shape allows
+ *   AMDP_OPT_GEMM_TILE               0 = the library's choice (default); 256, 128, 64 force that
+ *                                    matrix-core tile, BM*1000+BN (128064, 64128) the register-staged
+ *                                    kernel with that tile where it divides the product's shape;
+ *                                    -1 = generic kernel
+ *   AMDP_OPT_GEMM_TRANSPOSING_READS  1 (default) m/n-contiguous operands of the register-staged kernel
+ *                                    are read from LDS with the transposing read; 0 element by element
+ *   AMDP_OPT_GEMM_DIRECT_TO_LDS      1 (default), 2: plain products load their tiles from global memory
+ *                                    straight into LDS; 0: they take the register-staged or generic kernel
  *   AMDP_OPT_LAZY_JOIN               1 (default) a backward leaves its gradient leaves running on the
  *                                    side stream; 0 it ends by joining them
- *   AMDP_OPT_SPLIT_K_MIN_TOKENS      a weight-gradient product too small to give every compute unit a
- *                                    128x128 tile is split over its tokens into up to eight parts that
- *                                    are added in fixed order; a part contracts at least this many
- *                                    tokens (default 512, at least 64; a large value switches it off)
- *   AMDP_OPT_SPLIT_MAIN_MIN_K        a [tokens, d_model] product of the forward / dX chain whose 256x256
- *                                    tiles cover at most half of the compute units runs with its
- *                                    contraction split in two halves, added in order by a second
- *                                    kernel together with bias and residual, when a half is at least
- *                                    this long (default 3072, at least 64; a large value switches it off)
+ *   AMDP_OPT_SPLIT_K_MIN_TOKENS      by default the library splits the contraction of a product with few
+ *                                    output tiles into up to eight parts, added in fixed order, where its
+ *                                    estimate says that this is faster. A value set here replaces that
+ *                                    choice for weight gradients: a product too small to give every
+ *                                    compute unit a 128x128 tile is split over its tokens so that a part
+ *                                    contracts at least this many (at least 64; a large value: no split)
+ *   AMDP_OPT_SPLIT_MAIN_MIN_K        the same for products of the forward / dX chain: one whose 256x256
+ *                                    tiles cover at most half of the compute units runs in two halves,
+ *                                    added in order together with bias and residual, when a half is at
+ *                                    least this long (at least 64; a large value: no split)
  *   AMDP_OPT_LEAF_FORKS              with the side stream on, how often per layer a backward hands its
  *                                    parameter-gradient work to the side stream: 0 once per product
  *                                    (default below d_model 2048: every product starts as early as it

@@ -1,6 +1,6 @@
 // bf16 GEMM on the CDNA4 matrix cores (v_mfma_f32_32x32x16_bf16), fp32
 // accumulation. Tiles are staged through LDS (double buffered); one workgroup
-// = 4 wavefronts of 64 lanes arranged 2x2 over the BM x BN output tile.
+// = 4 or 8 wavefronts of 64 lanes arranged 2x2 or 2x4 over the BM x BN output tile.
 //
 // Operand storage, per template flag:
 //   A_KM = false : A is [M][K], k contiguous        (activations, dY)
@@ -16,11 +16,9 @@
 // Shapes must be whole tiles: M % BM == 0, N % BN == 0, K % 64 == 0, 16-byte
 // aligned rows; anything else takes the generic kernel.
 //
-// Two main-loop pipelines, chosen by tile size from measurement: tiles up to
-// 128x128 (<= 188 VGPRs, two workgroups per compute unit) keep fragments live
-// across the barrier so the matrix cores work through it; the 256x256 tile
-// (one wave per SIMD, 256 accumulator registers) cannot afford those extra
-// live registers and uses the simpler load / compute / store / barrier order.
+// This register-staged kernel serves what gemm_mfma_dl_kernel does not take: batched
+// products and products under a causal band (the attention form with its scores in
+// memory). Fragments stay live across the barrier so that the matrix cores work through it.
 #pragma once
 #include "common.h"
 
@@ -185,7 +183,6 @@ __global__ __launch_bounds__(128 * WGN) void gemm_mfma_kernel(GemmArgs g) {
     constexpr int NMF = TM * TN;                                                 // MFMAs per k-step
     constexpr int NVM = TA::NV + TB::NV;                                         // global loads / LDS writes per tile
 
-  if constexpr (BM * BN <= 128 * 128 || WGN == 4) {
     // Fragments are double buffered in registers: buffer kk&1 feeds k-step kk.
     bf16x8 va[2][TM], vb[2][TN];
     auto load_frags = [&](int buf, int stage, int kk) {
@@ -282,88 +279,6 @@ __global__ __launch_bounds__(128 * WGN) void gemm_mfma_kernel(GemmArgs g) {
         mfma_step(1);
     }
     __syncthreads();
-
-  } else {
-    if (nk > 0) {
-        TA::load(ra, pa, a_pass);
-        TB::load(rb, pb, b_pass);
-        TA::store(ra, sa);
-        TB::store(rb, sb);
-    }
-    __syncthreads();
-
-    // One k-tile of matrix work out of the LDS stage at byte offset `cur`.
-    // Fragments are double buffered in registers: the LDS reads of k-step kk+1
-    // are in flight while the matrix cores work on k-step kk.
-    auto compute_tile = [&](int cur) {
-        bf16x8 va[2][TM], vb[2][TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) va[0][i] = TA::template frag<TR>(fa + cur, i * 32, 0);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) vb[0][j] = TB::template frag<TR>(fb + cur, j * 32, 0);
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) {
-            const int c = kk & 1, n = c ^ 1;
-            if (kk + 1 < KSTEPS) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) va[n][i] = TA::template frag<TR>(fa + cur, i * 32, kk + 1);
-#pragma unroll
-                for (int j = 0; j < TN; ++j) vb[n][j] = TB::template frag<TR>(fb + cur, j * 32, kk + 1);
-            }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[c][i], vb[c][j], acc[i][j], 0, 0, 0);
-        }
-    };
-
-    // Steady state: while tile kt is multiplied, tile kt+1 travels global ->
-    // registers -> the other LDS stage. The loop body is one basic block; the
-    // scheduling directives at its end spread the memory instructions between
-    // the matrix instructions instead of letting them bunch up:
-    //   k-step 0: global loads of the next tile and LDS reads of k-step 1
-    //   k-steps 1..: LDS reads of the following k-step
-    //   last k-step: LDS writes of the next tile (its global loads are ~3 k-steps old)
-    for (int kt = 0; kt + 1 < nk; ++kt) {
-        const int cur = (kt & 1) * STAGE, nxt = STAGE - cur;
-        pa += a_step;
-        pb += b_step;
-        TA::load(ra, pa, a_pass);
-        TB::load(rb, pb, b_pass);
-        compute_tile(cur);
-        TA::store(ra, sa + nxt);
-        TB::store(rb, sb + nxt);
-        __builtin_amdgcn_sched_group_barrier(0x100, NDS, 0);
-        constexpr int NVM = TA::NV + TB::NV;
-#pragma unroll
-        for (int t = 0; t < NMF; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (t < NVM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            if (t < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        if (NVM > NMF) __builtin_amdgcn_sched_group_barrier(0x020, NVM - NMF, 0);
-#pragma unroll
-        for (int kk = 1; kk + 1 < KSTEPS; ++kk)
-#pragma unroll
-            for (int t = 0; t < NMF; ++t) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (t < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-#pragma unroll
-        for (int t = 0; t < NMF; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (t < NVM) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-        }
-        if (NVM > NMF) __builtin_amdgcn_sched_group_barrier(0x200, NVM - NMF, 0);
-        __syncthreads();
-    }
-    if (nk > 0) {
-        compute_tile(((nk - 1) & 1) * STAGE);
-        __syncthreads();
-    }
-
-  }
 
     // Epilogue through LDS: each wave parks one 32-row strip of its tile in LDS
     // as fp32, then reads it back row-wise so that every lane handles 8

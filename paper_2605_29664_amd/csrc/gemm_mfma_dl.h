@@ -1,12 +1,11 @@
 // bf16 GEMM on the matrix cores with tiles loaded from global memory STRAIGHT
-// INTO LDS (global_load_lds_dwordx4): no staging registers, no LDS-write
-// instructions, and the data of a tile is in flight for a whole k-tile of
-// matrix work. Same tiling, fragment double buffering, XCD-aware tile order and
-// epilogue as gemm_mfma_kernel; plain problems only (no batch, no causal band).
-// Measured on MI355X against the register-staged kernel: the four-wave 128x128
-// tile is 7-18 % faster in every layout once more than one workgroup per compute
-// unit is resident; the 256x256 tile gains 1-5 % for NT and TN and loses up to
-// 18 % for NN on wide-N shapes, so the stage keeps the staged kernel there.
+// INTO LDS (buffer_load_dwordx4 ... lds): no staging registers, no LDS-write
+// instructions, and the data of a tile is in flight for at least a whole k-tile
+// of matrix work. Same tiling, fragment double buffering, XCD-aware tile order and
+// epilogue as gemm_mfma_kernel; no batch, no causal band, but any M, N and K that
+// are multiples of 8 (the row kernels' vector width, so every shape a bf16 stage
+// can have): the loads go through buffer descriptors that end where the operand
+// ends, and a lane past the end writes zeros into the tile.
 //
 // One such load moves 64 lanes x 16 bytes = 1 KB to consecutive LDS addresses
 // (lane l's 16 bytes land at base + 16 l), so a tile row cannot be padded.
@@ -17,28 +16,54 @@
 //     16 bytes: chunk c of row r sits at chunk position c ^ ((r >> 1) & 7); a
 //     128-bit fragment read by 16 consecutive rows touches all 64 banks once;
 //   * m/n-contiguous operand, tile [64 k][R], R*2 bytes per row: the 64-byte
-//     block b of row k sits at block position b ^ (k & 3); the transposing read
-//     of half a wave (4 consecutive k, 64 bytes each) touches all banks once.
+//     block b of row k sits at block position b ^ (k & 3), with R = 64 (two
+//     blocks to a row) at b ^ ((k >> 1) & 1); the transposing read of half a
+//     wave (4 consecutive k, 64 bytes each) touches all banks once.
 #pragma once
 #include "gemm_mfma.h"
+#include <type_traits>
 
 namespace amdp {
 
-// 16 bytes per lane from global memory to LDS: lane l's data lands at
-// lds_addr + 16 l (lds_addr uniform, it travels in M0). Written as an asm
-// statement on purpose: with the compiler's own builtin its wait-count pass
-// puts a full vmcnt(0) wait in front of every transposing LDS read that follows
-// (it cannot tell that those read the other LDS stage), which serialises the
-// loads with the matrix work. The waits that are needed are written out below:
-// vmcnt(0) before the barrier that publishes a stage.
-// M0 is saved and restored around the load, so the statement leaves no
-// register the compiler reserves changed.
-__device__ __forceinline__ void load16_to_lds(const void* g, lds_u8* lds_addr) {
-    unsigned saved_m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(saved_m0)
-                 : "s"((unsigned)(__UINTPTR_TYPE__)lds_addr), "v"(g)
+// Buffer descriptor of `bytes` bytes at p (raw: range check on the byte offset).
+__device__ __forceinline__ u32x4 buffer_rsrc(const void* p, unsigned bytes) {
+    const uint64_t a = (uint64_t)p;
+    u32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    r[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xFFFFu);
+    r[2] = __builtin_amdgcn_readfirstlane(bytes);
+    r[3] = 0x00020000u;
+    return r;
+}
+constexpr unsigned BUF_OOB = 0x80000000u;      // a lane offset past the end of every descriptor used here (< 2 GiB)
+
+// 16 bytes per lane from rsrc + voff + soff to LDS: lane l's data lands at
+// lds_addr + 16 l (lds_addr uniform, it travels in M0); zeros for a lane whose
+// 16 bytes are not inside the descriptor. Written as an asm statement on
+// purpose: with the compiler's own builtin its wait-count pass puts a full
+// vmcnt(0) wait in front of every transposing LDS read that follows (it cannot
+// tell that those read another LDS slot), which serialises the loads with the
+// matrix work. The waits that are needed are written out below. M0 is a reserved
+// register: the compiler keeps no value in it across statements and sets it right
+// before each of its own uses, so it needs no restoring (saving and restoring it
+// cost 3 to 10 % of a 256x256 product's main loop in issue slots).
+__device__ __forceinline__ void load16_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, lds_u8* lds_addr) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"((unsigned)(__UINTPTR_TYPE__)lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
                  : "memory");
+}
+// s_barrier without the waits and fences of __syncthreads: what has to have
+// arrived is waited for explicitly; the compiler moves no memory access across it.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+// s_waitcnt vmcnt(N) alone (immediate: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+    static_assert(N >= 0 && N < 64);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
 // One operand's tile: R rows (m or n) by 64 k. NW = waves in the workgroup.
@@ -49,39 +74,34 @@ struct DlTile {
     static constexpr int CHUNK_ROWS = 1024 / ROWB;            // LDS rows per 1 KB load
     static constexpr int PW = BYTES / 1024 / NW;              // loads per wave
     static_assert(BYTES % (1024 * NW) == 0, "tile must split into whole 1 KB loads per wave");
-    static_assert(NW % 2 == 0 && (!KM || R == 128 || R == 256), "swizzle terms assume these shapes");
+    static_assert(NW % 2 == 0 && (!KM || R == 64 || R == 128 || R == 256), "swizzle terms assume these shapes");
+    __device__ static __forceinline__ int block_swizzle(int k) { return R == 64 ? (k >> 1) & 1 : k & 3; }
 
-    // Byte offset from the tile's first element (row 0, k 0) of what this lane
-    // fetches in pass 0; rs = elements between consecutive m/n rows, ks =
-    // elements between consecutive k.
-    // `valid` = rows of the tile that exist (a multiple of 64; R except in a
-    // ragged last tile). Rows beyond it are never stored, so their LDS content
-    // may be anything: a lane that would fetch them fetches an existing row
-    // instead (same address arithmetic, no access outside the matrix).
-    __device__ static __forceinline__ long lane_goff(int wave, int lane, long rs, long ks, int valid = R) {
+    // Byte offset, from the tile's first element (row 0, k 0), of what this lane
+    // fetches in pass p; ld = elements between the operand's memory rows (m/n rows
+    // of a k-contiguous operand, k rows of an m/n-contiguous one). `k_chunk`
+    // receives the lane's first k inside the tile (k-contiguous operand only; the
+    // same in every pass).
+    __device__ static __forceinline__ unsigned lane_goff(int wave, int lane, int p, unsigned ld, int& k_chunk) {
         if constexpr (!KM) {
-            const int row = 8 * wave + (lane >> 3), pos = lane & 7;
-            const int f = (row >> 1) & 7;
-            return (long)row * rs * 2 + ((pos ^ f) * 16);
+            const int row = 8 * (wave + NW * p) + (lane >> 3), pos = lane & 7;
+            const int c = pos ^ ((row >> 1) & 7);
+            k_chunk = 8 * c;
+            return (unsigned)row * ld * 2 + c * 16;
         } else {
             const int o = 16 * lane;                          // LDS byte inside the 1 KB chunk
-            const int krow = CHUNK_ROWS * wave + o / ROWB, pb = o % ROWB;
-            int b = (((pb >> 6) ^ (krow & 3)) << 6) | (pb & 63);
-            if (b >= valid * 2) b &= 127;                     // the first 64 rows always exist
-            return (long)krow * ks * 2 + b;
+            const int krow = CHUNK_ROWS * (wave + NW * p) + o / ROWB, pb = o % ROWB;
+            k_chunk = 0;
+            return (unsigned)krow * ld * 2 + ((((pb >> 6) ^ block_swizzle(krow)) << 6) | (pb & 63));
         }
     }
-    // Pass whose global rows pass p fetches: itself, or (k-contiguous operand, rows of
-    // the pass beyond `valid`) the pass that covers the same rows modulo 64.
-    __device__ static __forceinline__ int source_pass(int p, int valid) {
-        if constexpr (KM) return p;
-        else return p * 8 * NW < valid ? p : p % (64 / (8 * NW));
+    // Bytes of the operand from the tile's first element to the end of what the tile
+    // may read: `rows` m/n rows and K k exist from there on.
+    __device__ static __forceinline__ unsigned extent(int rows, int K, unsigned ld) {
+        if constexpr (!KM) return ((unsigned)(min(rows, R) - 1) * ld + (unsigned)K) * 2;
+        else return ((unsigned)(K - 1) * ld + (unsigned)rows) * 2;
     }
-    // pass p adds p * pass_gstride (the swizzle terms do not change with the pass)
-    __device__ static __forceinline__ long pass_gstride(long rs, long ks) {
-        return KM ? (long)CHUNK_ROWS * NW * ks * 2 : (long)8 * NW * rs * 2;
-    }
-    __device__ static __forceinline__ long ktile_gstride(long ks) { return KM ? (long)MF_BK * ks * 2 : MF_BK * 2; }
+    __device__ static __forceinline__ unsigned ktile_gstride(unsigned ld) { return KM ? MF_BK * ld * 2 : MF_BK * 2; }
 
     // Fragment addressing. `origin` = first row of the wave's part of the tile.
     // !KM: index = k-step (4 lane offsets), sub-tile j is an immediate.
@@ -92,9 +112,9 @@ struct DlTile {
             return (origin + r) * ROWB + (((2 * idx + half) ^ f) * 16);
         } else {
             const int q = lane >> 4, i = lane & 15;
-            const int krow = 8 * (q >> 1) + (i >> 2), sx = (i >> 2) & 3;
-            const int blk = (origin + 32 * idx) * 2 / 64;
-            return krow * ROWB + ((blk ^ sx) << 6) + (16 * (q & 1) + 4 * (i & 3)) * 2;
+            const int krow = 8 * (q >> 1) + (i >> 2);
+            const int blk = ((origin + 32 * idx) * 2 / 64) & (ROWB / 64 - 1);   // idx past the tile is never read
+            return krow * ROWB + ((blk ^ block_swizzle(krow)) << 6) + (16 * (q & 1) + 4 * (i & 3)) * 2;
         }
     }
     // f[] = lds + operand base + frag_off(origin, lane, 0..3)
@@ -111,17 +131,138 @@ struct DlTile {
     }
 };
 
-// EDGE: M and N need only be multiples of 64; the last tile of a row or column
-// of tiles is then ragged, loads of its missing rows are redirected (see
-// DlTile::lane_goff) and the epilogue skips them.
-template <int BM, int BN, bool A_KM, bool B_KM, int WGN, bool EDGE = false>
-__global__ __launch_bounds__(128 * WGN) void gemm_mfma_dl_kernel(GemmArgs g) {
-    constexpr int NT = 128 * WGN, NW = NT / 64;
-    constexpr int WM = BM / 2, WN = BN / WGN;
+// ---- epilogue ------------------------------------------------------------------
+// Each wave parks one 32-row strip of its tile in LDS as fp32 and reads it back
+// row-wise, so that a lane handles 8 consecutive columns (fp32 output: 4) and the
+// wave writes whole row segments. The strip is private to its wave and a wave's LDS
+// operations complete in issue order: no workgroup barrier between the passes. A
+// lane's columns are the same in every pass, so the bias is read once; what is read
+// per element (residual, GELU argument, the sum that is added to) is requested one
+// strip ahead, otherwise every pass waits for memory: with one workgroup per compute
+// unit the GELU' epilogue of a 4096 x 4096 product cost 28 us of its 53.
+enum EpiKind { EPI_BF16, EPI_RES, EPI_GELU_OUT, EPI_GELU_GRAD, EPI_F32, EPI_F32_ACC, EPI_MIXED };
+__device__ __forceinline__ EpiKind epilogue_kind(const Epilogue& e) {
+    if (e.out_f32) return e.bias || e.res || e.gelu_u || e.aux_out ? EPI_MIXED : e.accumulate ? EPI_F32_ACC : EPI_F32;
+    if (!e.res && !e.gelu_u && !e.aux_out) return EPI_BF16;
+    if (e.res && !e.gelu_u && !e.aux_out) return EPI_RES;
+    if (!e.res && !e.gelu_u && e.aux_out) return EPI_GELU_OUT;
+    if (!e.res && e.gelu_u && !e.aux_out && !e.bias) return EPI_GELU_GRAD;
+    return EPI_MIXED;
+}
+
+// acc: the wave's TM x TN accumulators; (m0, n0): its first row and column.
+template <int KIND, int TM, int TN>
+__device__ __forceinline__ void dl_epilogue(const GemmArgs& g, void* C, const f32x16 (&acc)[TM][TN], lds_f32* strip, int m0,
+                                            int n0, int lane) {
+    constexpr int WN = TN * 32, SW = WN + 4;
+    constexpr bool F32 = KIND == EPI_F32 || KIND == EPI_F32_ACC, SIDE = KIND == EPI_RES || KIND == EPI_GELU_GRAD;
+    constexpr int COLS = F32 ? 4 : 8, CPR = WN / COLS, RPP = 64 / CPR, NP = 32 / RPP;   // rows per pass, passes per strip
+    const int n = n0 + lane % CPR * COLS, r0 = lane / CPR;
+    const bool n_ok = n < g.N;
+    const Epilogue& e = g.epi;
+    float bias[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) bias[k] = 0.f;
+    if constexpr (!F32 && KIND != EPI_MIXED && KIND != EPI_GELU_GRAD)
+        if (e.bias && n_ok) {
+            const bf16x8 b = *(const bf16x8*)((const bf16*)e.bias + n);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) bias[k] = (float)b[k];
+        }
+    // what is read per element, one strip ahead (half a strip for the fp32 sum, which is twice as wide)
+    constexpr int NS = KIND == EPI_F32_ACC ? (NP > 8 ? 8 : NP) : NP;
+    bf16x8 side[2][SIDE ? NS : 1];
+    f32x4 sum[2][KIND == EPI_F32_ACC ? NS : 1];
+    const bf16* sp = KIND == EPI_RES ? (const bf16*)e.res : (const bf16*)e.gelu_u;
+    const long sld = KIND == EPI_RES ? e.ldr : e.ldu;
+    auto fetch = [&](int buf, int chunk) {        // chunk: NS passes
+#pragma unroll
+        for (int p = 0; p < NS; ++p) {
+            const long m = m0 + r0 + (chunk * NS + p) * RPP;
+            if constexpr (SIDE) side[buf][p] = n_ok && m < g.M ? *(const bf16x8*)(sp + m * sld + n) : bf16x8{};
+            if constexpr (KIND == EPI_F32_ACC)
+                sum[buf][p] = n_ok && m < g.M ? *(const f32x4*)((const float*)C + m * g.ldc + n) : f32x4{};
+        }
+    };
+    constexpr bool AHEAD = SIDE || KIND == EPI_F32_ACC;
+    if constexpr (AHEAD) fetch(0, 0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                strip[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SW + j * 32 + (lane & 31)] = acc[i][j][v];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int chunk = i * (NP / NS) + p / NS, buf = chunk & 1;
+            if constexpr (AHEAD)
+                if (p % NS == 0 && chunk + 1 < TM * (NP / NS)) fetch(buf ^ 1, chunk + 1);
+            const int row = r0 + p * RPP;
+            const long m = m0 + i * 32 + row;
+            if constexpr (F32) {
+                f32x4 v = *(lds_f32x4*)(strip + row * SW + lane % CPR * 4) * e.alpha;
+                if constexpr (KIND == EPI_F32_ACC) v = sum[buf][p % NS] + v;
+                if (n_ok && m < g.M) *(f32x4*)((float*)C + m * g.ldc + n) = v;
+            } else {
+                const f32x4 lo = *(lds_f32x4*)(strip + row * SW + lane % CPR * 8);
+                const f32x4 hi = *(lds_f32x4*)(strip + row * SW + lane % CPR * 8 + 4);
+                float v8[8];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) { v8[k] = lo[k]; v8[4 + k] = hi[k]; }
+                if constexpr (KIND == EPI_MIXED) {
+                    if (n_ok && m < g.M) epilogue_store8(e, C, g.ldc, m, n, v8);
+                } else {
+                    bf16x8 o, h;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        float v = v8[k] * e.alpha;
+                        if constexpr (KIND != EPI_GELU_GRAD) v += bias[k];
+                        if constexpr (KIND == EPI_RES) v += (float)side[buf][p % NS][k];
+                        if constexpr (KIND == EPI_GELU_GRAD) v *= gelu_grad_fast((float)side[buf][p % NS][k]);
+                        o[k] = (bf16)v;
+                        if constexpr (KIND == EPI_GELU_OUT) h[k] = (bf16)gelu_fast(v);
+                    }
+                    if (n_ok && m < g.M) {
+                        *(bf16x8*)((bf16*)C + m * g.ldc + n) = o;
+                        if constexpr (KIND == EPI_GELU_OUT) *(bf16x8*)((bf16*)e.aux_out + m * g.ldc + n) = h;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// ---- kernel --------------------------------------------------------------------
+// Workgroup: WGM x WGN waves over the BM x BN tile. LDS: RA slots for A tiles and RB
+// for B tiles (RA >= RB), refilled round robin. FD k-steps (16 k each) form a group;
+// a wave holds the fragments of two groups and reads the next one while the matrix
+// cores work on the current one.
+//
+// Schedule. Per k-tile kt there is ONE barrier, before its last group. By then every
+// wave has the rest of tile kt in registers, so its two slots are free, and tile
+// kt+1 has landed. The loads that fill them (B of tile kt+RB first: it is needed
+// soonest; then A of tile kt+RA) are spread one by one over a whole k-tile of
+// matrix instructions, and the LDS reads over the first three quarters of each
+// group; sched_barrier keeps the compiler from bunching them again. Both spreads
+// matter: a compute unit takes one 1 KB load per 16 cycles (64 bytes per cycle into
+// LDS), loads issued faster stall the wave and with it its matrix instructions.
+// LDS reads (256 bytes per cycle) and the loads' LDS writes do not disturb each
+// other. Measured on 8192^3, random data, same box: compiler-scheduled predecessor
+// (two stages, loads at once behind the barrier) 1205-1270 TFLOP/s by layout, this
+// schedule 1355-1400; matrix instructions alone 1740 (power-limited clock).
+//
+// grid.z parts: part z contracts k in [z * k_part, min(K, (z+1) * k_part)) into C + z * c_bo.
+template <int BM, int BN, bool A_KM, bool B_KM, int WGM, int WGN, int RA, int RB, int FD>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_dl_kernel(GemmArgs g, int k_part) {
+    constexpr int NW = WGM * WGN;
+    constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 32, TN = WN / 32;
     using TA = DlTile<BM, A_KM, NW>;
     using TB = DlTile<BN, B_KM, NW>;
-    constexpr int STAGE = TA::BYTES + TB::BYTES;
+    static_assert(RA >= RB && RB >= 2);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     lds_u8* lds = (lds_u8*)smem_raw;
 
@@ -129,9 +270,12 @@ __global__ __launch_bounds__(128 * WGN) void gemm_mfma_dl_kernel(GemmArgs g) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
 
+    // tile id -> (pm, pn): a contiguous run of tiles per XCD (workgroups are dealt round
+    // robin to the 8 XCDs, each with its own L2), then groups of 8 row-tiles walked
+    // column by column so that neighbours share operand tiles
     const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
-    int pid = blockIdx.x;
-    if (ntiles % 8 == 0) pid = (pid % 8) * (ntiles / 8) + pid / 8;
+    const int xcd = blockIdx.x % 8;
+    const int pid = xcd * (ntiles / 8) + min(xcd, ntiles % 8) + blockIdx.x / 8;
     constexpr int GROUP = 8;
     const int per_group = GROUP * tiles_n;
     const int first_m = (pid / per_group) * GROUP;
@@ -140,20 +284,49 @@ __global__ __launch_bounds__(128 * WGN) void gemm_mfma_dl_kernel(GemmArgs g) {
     const int pn = (pid % per_group) / gsize;
     const int m0 = pm * BM, n0 = pn * BN;
 
-    const int valid_m = EDGE ? min(BM, g.M - m0) : BM, valid_n = EDGE ? min(BN, g.N - n0) : BN;
-    const char* pa = (const char*)((const bf16*)g.A + (long)m0 * g.a_rs) + TA::lane_goff(wave, lane, g.a_rs, g.a_cs, valid_m);
-    const char* pb = (const char*)((const bf16*)g.B + (long)n0 * g.b_cs) + TB::lane_goff(wave, lane, g.b_cs, g.b_rs, valid_n);
-    const long a_pass = TA::pass_gstride(g.a_rs, g.a_cs), b_pass = TB::pass_gstride(g.b_cs, g.b_rs);
-    const long a_step = TA::ktile_gstride(g.a_cs), b_step = TB::ktile_gstride(g.b_rs);
-    auto issue_tile = [&](int stage) {
+    const int k_lo = blockIdx.z * k_part, K = min(k_part, g.K - k_lo);
+    const unsigned lda = (unsigned)(A_KM ? g.a_cs : g.a_rs), ldb = (unsigned)(B_KM ? g.b_rs : g.b_cs);
+    // A tile's missing rows lie past its descriptor's end. So do the missing k of an
+    // m/n-contiguous operand; those of a k-contiguous one are the next row's first
+    // elements, so its lanes past K are sent past the end.
+    u32x4 ra = buffer_rsrc((const bf16*)g.A + (long)m0 * g.a_rs + (long)k_lo * g.a_cs, TA::extent(g.M - m0, K, lda));
+    u32x4 rb = buffer_rsrc((const bf16*)g.B + (long)n0 * g.b_cs + (long)k_lo * g.b_rs, TB::extent(g.N - n0, K, ldb));
+    unsigned va_off[TA::PW], vb_off[TB::PW];
+    int ka, kb;
 #pragma unroll
-        for (int p = 0; p < TA::PW; ++p)
-            load16_to_lds(pa + (EDGE ? TA::source_pass(p, valid_m) : p) * a_pass, lds + stage + (wave + NW * p) * 1024);
+    for (int p = 0; p < TA::PW; ++p) va_off[p] = TA::lane_goff(wave, lane, p, lda, ka);
 #pragma unroll
-        for (int p = 0; p < TB::PW; ++p)
-            load16_to_lds(pb + (EDGE ? TB::source_pass(p, valid_n) : p) * b_pass, lds + stage + TA::BYTES + (wave + NW * p) * 1024);
-        pa += a_step;
-        pb += b_step;
+    for (int p = 0; p < TB::PW; ++p) vb_off[p] = TB::lane_goff(wave, lane, p, ldb, kb);
+    unsigned sa_off = 0, sb_off = 0;
+    const unsigned a_step = TA::ktile_gstride(lda), b_step = TB::ktile_gstride(ldb);
+    const int nk = (K + MF_BK - 1) / MF_BK;
+    constexpr int NVM = TA::PW + TB::PW;
+    constexpr int A_BYTES = RA * TA::BYTES;
+    int ka_issue = 0, kb_issue = 0;            // first k of the operand tile being issued
+    int a_slot = 0, b_slot = A_BYTES;          // where it goes
+    auto issue_a = [&](int p) {
+        const unsigned v = (!A_KM && ka_issue + ka >= K) ? BUF_OOB : va_off[p];
+        load16_to_lds(ra, v, sa_off, lds + a_slot + (wave + NW * p) * 1024);
+    };
+    auto issue_b = [&](int p) {
+        const unsigned v = (!B_KM && kb_issue + kb >= K) ? BUF_OOB : vb_off[p];
+        load16_to_lds(rb, v, sb_off, lds + b_slot + (wave + NW * p) * 1024);
+    };
+    // tiles past the last are issued with an empty descriptor and offset 0 (zeros, no memory
+    // traffic): the loop body has no branches and the count of loads in flight is fixed
+    auto next_a = [&]() {
+        ka_issue += MF_BK;
+        const bool more = ka_issue < K;
+        sa_off = more ? sa_off + a_step : 0;
+        if (!more) ra[2] = 0;
+        a_slot = a_slot + TA::BYTES == A_BYTES ? 0 : a_slot + TA::BYTES;
+    };
+    auto next_b = [&]() {
+        kb_issue += MF_BK;
+        const bool more = kb_issue < K;
+        sb_off = more ? sb_off + b_step : 0;
+        if (!more) rb[2] = 0;
+        b_slot = b_slot + TB::BYTES == A_BYTES + RB * TB::BYTES ? A_BYTES : b_slot + TB::BYTES;
     };
 
     lds_u8* fa[4];
@@ -161,7 +334,7 @@ __global__ __launch_bounds__(128 * WGN) void gemm_mfma_dl_kernel(GemmArgs g) {
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         fa[x] = lds + TA::frag_off(wm * WM, lane, x);
-        fb[x] = lds + TA::BYTES + TB::frag_off(wn * WN, lane, x);
+        fb[x] = lds + A_BYTES + TB::frag_off(wn * WN, lane, x);
     }
 
     f32x16 acc[TM][TN];
@@ -172,133 +345,134 @@ __global__ __launch_bounds__(128 * WGN) void gemm_mfma_dl_kernel(GemmArgs g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    const int nk = g.K / MF_BK;
-    constexpr int NDS = TM * (A_KM ? 2 : 1) + TN * (B_KM ? 2 : 1), NMF = TM * TN, NVM = TA::PW + TB::PW;
+    constexpr int G = 4 / FD;                  // groups per k-tile
+    constexpr int NR = FD * (TM + TN);         // fragments per group
+    constexpr int NM = FD * TM * TN;           // matrix instructions per group
+    bf16x8 va[2][FD][TM], vb[2][FD][TN];
+    auto read_frag = [&](int set, int sa, int sb, int grp, int r) {     // fragment r of group grp
+        const int f = r / (TM + TN), x = r % (TM + TN), kk = grp * FD + f;
+        if (x < TM) va[set][f][x] = TA::frag(fa, sa, x, kk);
+        else vb[set][f][x - TM] = TB::frag(fb, sb, x - TM, kk);
+    };
 
-    bf16x8 va[2][TM], vb[2][TN];
-    auto load_frags = [&](int buf, int stage, int kk) {
+    // Loads that may still be on their way at the barrier of k-tile kt, before which A and B of tile
+    // kt+1 must have landed: those issued behind them (B(j+RB), then A(j+RA) per barrier j < kt).
+    constexpr int IN_FLIGHT = (RA > RB ? TA::PW : 0) + (RB - 2) * NVM;
+    static_assert(IN_FLIGHT + NVM < 64, "vmcnt counts to 63");
 #pragma unroll
-        for (int i = 0; i < TM; ++i) va[buf][i] = TA::frag(fa, stage, i, kk);
+    for (int j = -RA; j < 0; ++j) {
+        const int upto = j == -1 ? NVM / G : NVM;      // the rest of barrier -1's loads go out in the first groups below
+        if (j + RB >= 0) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) vb[buf][j] = TB::frag(fb, stage, j, kk);
-    };
-    auto mfma_step = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[buf][i], vb[buf][j], acc[i][j], 0, 0, 0);
-    };
-    auto interleave_reads = [&]() {
-#pragma unroll
-        for (int t = 0; t < NMF; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (t < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            for (int p = 0; p < TB::PW; ++p)
+                if (p < upto) issue_b(p);
+            if (upto >= TB::PW) next_b();
         }
-        if (NDS > NMF) __builtin_amdgcn_sched_group_barrier(0x100, NDS - NMF, 0);
-    };
+#pragma unroll
+        for (int p = 0; p < TA::PW; ++p)
+            if (TB::PW + p < upto) issue_a(p);
+        if (upto == NVM) next_a();
+    }
+    wait_vmcnt<IN_FLIGHT + NVM / G>();
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read_frag(0, 0, 0, 0, r);
 
-    // Tiles 0 and 1 travel first; tile kt+2 is issued at the barrier inside
-    // iteration kt, when every wave is done with the stage it goes to.
-    // s_waitcnt immediate: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8.
-    if (nk > 0) issue_tile(0);
-    if (nk > 1) {
-        issue_tile(STAGE);
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (NVM & 15) | ((NVM >> 4) << 14));   // vmcnt(NVM): tile 0 has landed
+    int cur_a = 0, nxt_a = TA::BYTES, cur_b = 0, nxt_b = TB::BYTES;     // slots of tiles kt and kt+1
+    auto group = [&](auto set_c, auto grp_c) {
+        constexpr int S = decltype(set_c)::value, GR = decltype(grp_c)::value;
+        constexpr bool last = GR == G - 1;
+        if constexpr (last) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wave's reads of tile kt, issued a group ago
+            wait_vmcnt<IN_FLIGHT>();                 // tile kt+1 has landed
+            lds_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const int rsa = last ? nxt_a : cur_a, rsb = last ? nxt_b : cur_b;
+        constexpr int rgrp = last ? 0 : GR + 1;
+        constexpr int POS = last ? 0 : GR + 1, L0 = POS * NVM / G, L1 = (POS + 1) * NVM / G;
+        int r = 0, l = L0;
+#pragma unroll
+        for (int t = 0; t < NM; ++t) {
+            const int f = t / (TM * TN), i = t % (TM * TN) / TN, j = t % TN;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[S][f][i], vb[S][f][j], acc[i][j], 0, 0, 0);
+            const int r_to = min(NR, ((t + 1) * NR * 4 + 3 * NM - 1) / (3 * NM));
+            for (; r < r_to; ++r) read_frag(S ^ 1, rsa, rsb, rgrp, r);
+            const int l_to = min(L1, L0 + ((t + 1) * (L1 - L0) + NM - 1) / NM);
+            for (; l < l_to; ++l) { if (l < TB::PW) issue_b(l); else issue_a(l - TB::PW); }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (L0 < TB::PW && L1 >= TB::PW) next_b();
+        if constexpr (L1 == NVM) next_a();
+    };
+    auto advance = [&]() {
+        cur_a = nxt_a; nxt_a = nxt_a + TA::BYTES == A_BYTES ? 0 : nxt_a + TA::BYTES;
+        cur_b = nxt_b; nxt_b = nxt_b + TB::BYTES == RB * TB::BYTES ? 0 : nxt_b + TB::BYTES;
+    };
+    using std::integral_constant;
+    typedef integral_constant<int, 0> I0;
+    typedef integral_constant<int, 1> I1;
+    if constexpr (FD == 4) {
+        int kt = 0;
+        for (; kt + 1 < nk; kt += 2) {
+            group(I0{}, I0{}); advance();
+            group(I1{}, I0{}); advance();
+        }
+        if (kt < nk) group(I0{}, I0{});
     } else {
-        __builtin_amdgcn_s_waitcnt(0x0F70);                                     // vmcnt(0)
-    }
-    __syncthreads();
-    if (nk > 0) load_frags(0, 0, 0);
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = (kt & 1) * STAGE, nxt = STAGE - cur;
-        load_frags(1, cur, 1);
-        mfma_step(0);
-        interleave_reads();
-        load_frags(0, cur, 2);
-        mfma_step(1);
-        interleave_reads();
-        load_frags(1, cur, 3);
-        mfma_step(0);
-        interleave_reads();
-        // tile kt+1 has landed (it is the only one in flight) and this wave's reads of
-        // the current stage are done: after the barrier the stage can be refilled
-        __builtin_amdgcn_s_waitcnt(0);                               // vmcnt(0) expcnt(0) lgkmcnt(0)
-        __syncthreads();
-        if (kt + 2 < nk) issue_tile(cur);
-        if (kt + 1 < nk) load_frags(0, nxt, 0);
-        mfma_step(1);
-#pragma unroll
-        for (int t = 0; t < NMF; ++t) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (t < NVM) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-            if (t < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        static_assert(FD == 1, "one k-step or a whole k-tile to a group");
+        for (int kt = 0; kt < nk; ++kt) {
+            group(I0{}, I0{});
+            group(I1{}, I1{});
+            group(I0{}, integral_constant<int, 2>{});
+            group(I1{}, integral_constant<int, 3>{}); advance();
         }
     }
+    wait_vmcnt<0>();           // the empty tiles' zeros are in LDS before the epilogue reuses it
     __syncthreads();
 
-    // Epilogue through LDS, as in gemm_mfma_kernel.
-    void* C = g.C;
-    constexpr int SW = WN + 4;
-    lds_f32* strip = (lds_f32*)lds + wave * (32 * SW);
-    const bool plain_f32 = epilogue_is_plain_f32(g.epi);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        __builtin_amdgcn_wave_barrier();   // wave-private strip: no workgroup barrier needed (see gemm_mfma_kernel)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                strip[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * SW + j * 32 + (lane & 31)] = acc[i][j][v];
-        __builtin_amdgcn_wave_barrier();
-        if (plain_f32) {
-            constexpr int QPR = WN / 4;            // column quads per strip row
-            for (int it = 0; it < WN / 8; ++it) {
-                const int c = lane + 64 * it;
-                const int row = c / QPR, cq = c % QPR;
-                const f32x4 v4 = *(lds_f32x4*)(strip + row * SW + cq * 4);
-                const long m = m0 + wm * WM + i * 32 + row;
-                const long n = n0 + wn * WN + cq * 4;
-                if (!EDGE || (m < g.M && n < g.N)) epilogue_store4_f32(g.epi, C, g.ldc, m, n, v4);
-            }
-            continue;
-        }
-        constexpr int CPR = WN / 8;
-        for (int it = 0; it < WN / 16; ++it) {
-            const int c = lane + 64 * it;
-            const int row = c / CPR, cc = c % CPR;
-            float v8[8];
-            const f32x4 lo = *(lds_f32x4*)(strip + row * SW + cc * 8);
-            const f32x4 hi = *(lds_f32x4*)(strip + row * SW + cc * 8 + 4);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) { v8[k] = lo[k]; v8[4 + k] = hi[k]; }
-            const long m = m0 + wm * WM + i * 32 + row;
-            const long n = n0 + wn * WN + cc * 8;
-            if (!EDGE || (m < g.M && n < g.N)) epilogue_store8(g.epi, C, g.ldc, m, n, v8);
-        }
+    void* C = g.epi.out_f32 ? (void*)((float*)g.C + blockIdx.z * g.c_bo) : (void*)((bf16*)g.C + blockIdx.z * g.c_bo);
+    lds_f32* strip = (lds_f32*)lds + wave * (32 * (WN + 4));
+    const int mw = m0 + wm * WM, nw = n0 + wn * WN;
+    // the kinds a layout is used with get their own code; anything else takes the mixed form
+    const EpiKind kind = epilogue_kind(g.epi);
+    if constexpr (A_KM) {
+        if (kind == EPI_F32) { dl_epilogue<EPI_F32, TM, TN>(g, C, acc, strip, mw, nw, lane); return; }
+        if (kind == EPI_F32_ACC) { dl_epilogue<EPI_F32_ACC, TM, TN>(g, C, acc, strip, mw, nw, lane); return; }
+    } else {
+        if (kind == EPI_BF16) { dl_epilogue<EPI_BF16, TM, TN>(g, C, acc, strip, mw, nw, lane); return; }
+        if (kind == EPI_RES) { dl_epilogue<EPI_RES, TM, TN>(g, C, acc, strip, mw, nw, lane); return; }
+        if (kind == EPI_F32) { dl_epilogue<EPI_F32, TM, TN>(g, C, acc, strip, mw, nw, lane); return; }     // parts of a split contraction
+        if (B_KM && kind == EPI_GELU_OUT) { dl_epilogue<EPI_GELU_OUT, TM, TN>(g, C, acc, strip, mw, nw, lane); return; }
+        if (!B_KM && kind == EPI_GELU_GRAD) { dl_epilogue<EPI_GELU_GRAD, TM, TN>(g, C, acc, strip, mw, nw, lane); return; }
     }
+    dl_epilogue<EPI_MIXED, TM, TN>(g, C, acc, strip, mw, nw, lane);
 }
 
-// Conditions beyond mfma_shape_ok: a plain problem, no batch, no causal band.
-template <int BM, int BN>
+// True when the problem satisfies every assumption of gemm_mfma_dl_kernel (any tile):
+// whole 16-byte vectors along every row, and every descriptor below 2 GiB.
 inline bool mfma_dl_shape_ok(const GemmArgs& g, bool a_km, bool b_km) {
-    return mfma_shape_ok<BM, BN>(g, a_km, b_km) && g.batch == 1 && g.causal == 0;
+    GemmArgs t = g;
+    if (g.M % 8 || g.N % 8 || g.K % 8 || g.M <= 0 || g.N <= 0 || g.K <= 0 || g.batch != 1 || g.causal) return false;
+    t.M = t.N = 64; t.K = MF_BK;
+    if (!mfma_shape_ok<64, 64>(t, a_km, b_km)) return false;
+    const long lda = a_km ? g.a_cs : g.a_rs, ldb = b_km ? g.b_rs : g.b_cs;
+    const long ea = a_km ? g.K * lda + g.M : 256 * lda + g.K, eb = b_km ? g.K * ldb + g.N : 256 * ldb + g.K;
+    constexpr long LIM = (1L << 30) - 4096 * 64;      // elements: 2 GiB less one k-tile's overshoot of the scalar offset
+    return ea < LIM && eb < LIM && lda < (1 << 22) && ldb < (1 << 22);
 }
 
-// The EDGE instantiation's conditions: as mfma_dl_shape_ok, with M and N multiples
-// of 64 instead of the tile.
-inline bool mfma_dl_edge_shape_ok(const GemmArgs& g, bool a_km, bool b_km) {
-    return mfma_shape_ok<64, 64>(g, a_km, b_km) && g.batch == 1 && g.causal == 0;
-}
-
-template <int BM, int BN, bool A_KM, bool B_KM, int WGN, bool EDGE = false>
-inline hipError_t launch_gemm_mfma_dl(const GemmArgs& g, hipStream_t st) {
-    constexpr size_t lds = 2 * (size_t)(BM + BN) * MF_BK * 2;
+// parts > 1: split contraction, fp32 parts at C + z * g.c_bo; k_part a multiple of MF_BK with
+// (parts - 1) * k_part < K.
+template <int BM, int BN, bool A_KM, bool B_KM, int WGM, int WGN, int RA, int RB, int FD>
+inline hipError_t launch_gemm_mfma_dl(const GemmArgs& g, hipStream_t st, int parts = 1, int k_part = 0) {
+    constexpr size_t lds = (size_t)(RA * BM + RB * BN) * MF_BK * 2;
     static_assert(lds <= 160 * 1024, "tile does not fit the 160 KB LDS of a CDNA4 compute unit");
-    constexpr auto kern = gemm_mfma_dl_kernel<BM, BN, A_KM, B_KM, WGN, EDGE>;
+    static_assert((size_t)WGM * WGN * 32 * (BN / WGN + 4) * 4 <= lds, "the epilogue's strips reuse the slots");
+    constexpr auto kern = gemm_mfma_dl_kernel<BM, BN, A_KM, B_KM, WGM, WGN, RA, RB, FD>;
     if (hipError_t e = allow_dynamic_lds<kern>((int)lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN)), dim3(128 * WGN), lds, st, g);
+    hipLaunchKernelGGL(kern, dim3(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN), 1, parts), dim3(64 * WGM * WGN), lds, st, g,
+                       parts > 1 ? k_part : g.K);
     return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@
 #include "common.h"
 #include "gemm_mfma.h"
 #include "gemm_mfma_dl.h"
+#include "gemm_plan.h"
 #include "gemm_simple.h"
 #include "rowwise.h"
 #include "streaming.h"
@@ -188,15 +189,26 @@ void carve(const Dims& d, const amdp_stage_config_t& c, Carve* w) {
         const size_t NDp = pk ? (size_t)d.N * d.H * flash_head_dim(d) * d.esz : 0;
         w->pk_qkv = take(3 * NDp); w->pk_dqkv = take(3 * NDp); w->pk_o = take(NDp); w->pk_do = take(NDp);
     }
-    // Only the D x D product of a narrow layer is ever split (the others have three to
-    // sixteen times as many tiles); room for eight parts while its 128x128 tiles would
-    // leave half of a 256-unit GPU idle.
+    // Scratch of products whose contraction is split into parts (gemm_plan.h): one for the
+    // weight gradients, which may run on the side stream, one for the main chain. Sized for
+    // what the plan of a 256-unit GPU wants of this stage's products and for the forced splits
+    // of AMDP_OPT_SPLIT_K_MIN_TOKENS and AMDP_OPT_SPLIT_MAIN_MIN_K.
     w->splitk_bytes = (d.bf && d.D % 128 == 0 && (long)(d.D / 128) * (d.D / 128) * 2 <= 256) ? (size_t)8 * d.D * d.D * 4 : 0;
-    w->splitk = take(w->splitk_bytes);
-    // [tokens, d_model] outputs whose 256x256 tiles cover at most half of a 256-unit GPU may run with
-    // their contraction split in two (main_split): two fp32 copies of the output
     w->splitm_bytes = (d.bf && d.N % 256 == 0 && d.D % 256 == 0 && (long)(d.N / 256) * (d.D / 256) * 2 <= 256)
                           ? (size_t)2 * d.N * d.D * 4 : 0;
+    if (d.bf) {
+        auto need = [](long M, long N, long K) {
+            const DlPlan p = dl_plan(M, N, K, true, true, SIZE_MAX, 256);
+            return p.parts > 1 ? (size_t)M * N * 4 * p.parts : (size_t)0;
+        };
+        const size_t dw[] = {need(d.D, 3L * d.D, d.N), need(d.D, d.D, d.N), need(d.D, d.F, d.N), need(d.F, d.D, d.N),
+                             d.lm ? need(d.Vld, d.D, d.N) : 0};
+        const size_t mc[] = {need(d.N, 3L * d.D, d.D), need(d.N, d.D, d.D), need(d.N, d.D, d.F), need(d.N, d.D, 3L * d.D),
+                             d.lm ? need(d.N, d.Vld, d.D) : 0, d.lm ? need(d.N, d.D, d.Vld) : 0};
+        for (size_t n : dw) w->splitk_bytes = std::max(w->splitk_bytes, n);
+        for (size_t n : mc) w->splitm_bytes = std::max(w->splitm_bytes, n);
+    }
+    w->splitk = take(w->splitk_bytes);
     w->splitm = take(w->splitm_bytes);
     w->partial_chunks = 256;
     // one row of partial sums per row chunk for all six column reductions of a layer's backward
@@ -239,8 +251,7 @@ struct amdp_stage {
     int staged_slot = -1;   // activation slot whose gradient sits in the staging buffer
     bool use_tr = true;
     int force_tile = 0;
-    int use_direct = 1;           // plain products load tiles straight into LDS where measured faster
-                                  // (AMDP_OPT_GEMM_DIRECT_TO_LDS; 0: never, always through registers; 2: wherever the shape allows)
+    int use_direct = 1;           // AMDP_OPT_GEMM_DIRECT_TO_LDS; 0: plain products through the register-staged kernel
     Profiler prof;
     // Launch target of the helper functions: the caller's stream, or the side
     // stream while a gradient leaf (dW GEMM, bias / LayerNorm column sums) is
@@ -266,8 +277,10 @@ struct amdp_stage {
     bool overlap = true;
     int leaf_forks = 0;            // side-stream forks per layer of a backward: 0 = one per leaf, 1, 2 (set at creation)
     bool fused_acc = false;        // backward adds parameter gradients into G directly
-    int splitk_min_k = 512;        // fewest tokens a part of a split weight-gradient product contracts
-    int split_main_min_k = 3072;   // shortest half of a main-chain contraction that is worth splitting
+    // 0: the plan decides where contractions are split (gemm_plan.h); set by AMDP_OPT_SPLIT_K_MIN_TOKENS /
+    // AMDP_OPT_SPLIT_MAIN_MIN_K: the fixed rules described there, with this shortest part
+    int splitk_min_k = 0;
+    int split_main_min_k = 0;
     bool flash = true;      // fused attention kernels (shape permitting); false: scores, softmax, probabilities in HBM
     hipEvent_t next_event() { ev_next = (ev_next + 1) % 16; return events[ev_next]; }
 
@@ -362,22 +375,18 @@ hipError_t launch_tile(amdp_stage* st, const GemmArgs& g) {
                       : launch_gemm_mfma_inst<BM, BN, A_KM, B_KM, false, WGN>(g, st->launch);
 }
 
-// Tile choice, from measurement on MI355X: the largest tile that still fills
-// the GPU wins (the 256x256 tile needs a workgroup for every compute unit and
-// at least 70 % of its last round of workgroups, the smaller ones three
-// quarters of the units); when no tile gets there, the one with the most
-// workgroups does. Plain products (no batch, no causal band) whose M or N is a
-// multiple of 64 but not of the tile run the 128x128 and 256x256 tiles with a
-// ragged last tile on the direct-to-LDS kernel.
+// Batched products and products under a causal band (the attention form with its scores
+// in memory), and any product while AMDP_OPT_GEMM_DIRECT_TO_LDS is 0 or a rectangular tile
+// is asked for: the register-staged kernel where a tile divides the shape, else the generic
+// one. The largest tile that fills the GPU wins (256x256: a workgroup for every compute unit and
+// at least 70 % of its last round of workgroups; the smaller ones three quarters of the
+// units); when no tile gets there, the one with the most workgroups does.
 template <bool A_KM, bool B_KM>
-int gemm_bf16_layout(amdp_stage* st, const GemmArgs& g) {
-    const bool direct = st->use_direct && g.batch == 1 && g.causal == 0, always = st->use_direct == 2;
-    const bool ragged_ok = direct && mfma_dl_edge_shape_ok(g, A_KM, B_KM);
-    struct Cand { int bm, bn; bool exact, ok; };
-    Cand cand[5] = {{256, 256, mfma_shape_ok<256, 256>(g, A_KM, B_KM), false}, {128, 128, mfma_shape_ok<128, 128>(g, A_KM, B_KM), false},
-                    {128, 64, mfma_shape_ok<128, 64>(g, A_KM, B_KM), false},   {64, 128, mfma_shape_ok<64, 128>(g, A_KM, B_KM), false},
-                    {64, 64, mfma_shape_ok<64, 64>(g, A_KM, B_KM), false}};
-    for (int i = 0; i < 5; ++i) cand[i].ok = cand[i].exact || (i < 2 && ragged_ok);
+int gemm_bf16_staged(amdp_stage* st, const GemmArgs& g) {
+    struct Cand { int bm, bn; bool ok; };
+    const Cand cand[5] = {{256, 256, mfma_shape_ok<256, 256>(g, A_KM, B_KM)}, {128, 128, mfma_shape_ok<128, 128>(g, A_KM, B_KM)},
+                          {128, 64, mfma_shape_ok<128, 64>(g, A_KM, B_KM)},   {64, 128, mfma_shape_ok<64, 128>(g, A_KM, B_KM)},
+                          {64, 64, mfma_shape_ok<64, 64>(g, A_KM, B_KM)}};
     auto tiles = [&](const Cand& c) { return (long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn) * g.batch; };
     auto fills = [&](int i) {
         const long t = tiles(cand[i]);
@@ -397,31 +406,13 @@ int gemm_bf16_layout(amdp_stage* st, const GemmArgs& g) {
                                (cand[i].bm == cand[i].bn && cand[i].bm == st->force_tile))) pick = i;
     if (st->force_tile < 0) pick = -1;
     char name[48];
+    const char* layout = A_KM ? "TN" : (B_KM ? "NN" : "NT");
     if (pick >= 0)
-        snprintf(name, sizeof(name), "gemm_mfma%dx%d_%s%s", cand[pick].bm, cand[pick].bn,
-                 A_KM ? "TN" : (B_KM ? "NN" : "NT"), g.batch > 1 ? "_batched" : "");
+        snprintf(name, sizeof(name), "gemm_mfma%dx%d_%s%s", cand[pick].bm, cand[pick].bn, layout, g.batch > 1 ? "_batched" : "");
     else
-        snprintf(name, sizeof(name), "gemm_generic_%s%s", A_KM ? "TN" : (B_KM ? "NN" : "NT"), g.batch > 1 ? "_batched" : "");
+        snprintf(name, sizeof(name), "gemm_generic_%s%s", layout, g.batch > 1 ? "_batched" : "");
     ProfScope ps(st, name, gemm_flops(g), 0.0);
     hipError_t e;
-    if (pick >= 0 && pick < 2 && !cand[pick].exact) {
-        e = pick == 0 ? launch_gemm_mfma_dl<256, 256, A_KM, B_KM, 4, true>(g, st->launch)
-                      : launch_gemm_mfma_dl<128, 128, A_KM, B_KM, 2, true>(g, st->launch);
-        return hip_ok(e, name) ? AMDP_OK : AMDP_E_HIP;
-    }
-    // Plain products load their tiles straight into LDS where that measured faster: the
-    // 128x128 tile in every layout once more than one workgroup per compute unit is
-    // resident (7-18 %; with fewer the eight-wave kernel below stays ahead), the
-    // 256x256 tile for NT and TN (1-5 %; NN measured up to 18 % slower there).
-    constexpr bool NN_LAYOUT = !A_KM && B_KM;
-    if (direct && pick == 0 && (!NN_LAYOUT || always)) {
-        e = launch_gemm_mfma_dl<256, 256, A_KM, B_KM, 4>(g, st->launch);
-        return hip_ok(e, name) ? AMDP_OK : AMDP_E_HIP;
-    }
-    if (direct && pick == 1 && (tiles(cand[1]) > st->n_cu || always)) {
-        e = launch_gemm_mfma_dl<128, 128, A_KM, B_KM, 2>(g, st->launch);
-        return hip_ok(e, name) ? AMDP_OK : AMDP_E_HIP;
-    }
     switch (pick) {
         case 0: e = launch_tile<256, 256, A_KM, B_KM, 4>(st, g); break;   // eight waves (two per SIMD), each 128x64 of the tile
         case 1:
@@ -439,49 +430,75 @@ int gemm_bf16_layout(amdp_stage* st, const GemmArgs& g) {
     return hip_ok(e, name) ? AMDP_OK : AMDP_E_HIP;
 }
 
-enum GemmLayout { G_NN, G_NT, G_TN };
-
-// A bf16-output product on the main chain whose 256x256 tiles would cover at most
-// half of the compute units, with a long contraction: the contraction is split
-// in two so that every unit gets a 256x256 tile (one batched launch into fp32
-// scratch), and a second kernel adds the parts in order and applies bias and
-// residual. Measured on configuration 5's 2048 x 4096 outputs with operands that
-// are not cache-resident, against the 128x128 tile at two workgroups per unit:
-// +15 to +19 % at contractions of 12288 and 16384, -6 to -10 % at 4096; on
-// configuration 4's 4096 x 2048 outputs +0.5 to +13 % at 8192, +6 to +7 % at 6144,
-// -22 to -25 % at 2048. Hence: a half must be at least 3072 long.
-int main_split(const amdp_stage* st, const GemmArgs& g, bool a_km, bool b_km) {
-    if (!st->d.bf || st->force_tile != 0 || g.batch != 1 || g.causal || g.epi.out_f32 || g.epi.gelu_u || g.epi.aux_out)
-        return 1;
-    if (g.M % 256 || g.N % 256 || g.ldc != g.N || (g.epi.res && g.epi.ldr != g.N) || g.epi.alpha != 1.0f) return 1;
-    const long tiles = (long)(g.M / 256) * (g.N / 256);
-    if (tiles * 2 > st->n_cu || g.K % (2 * MF_BK) || g.K / 2 < st->split_main_min_k) return 1;
-    if ((size_t)g.M * g.N * 4 * 2 > st->w.splitm_bytes) return 1;
-    GemmArgs part = g;
-    part.K = g.K / 2;
-    return mfma_shape_ok<256, 256>(part, a_km, b_km) ? 2 : 1;
-}
 template <bool A_KM, bool B_KM>
-int gemm_main_split(amdp_stage* st, GemmArgs g, int ways) {
-    const Epilogue epi = g.epi;
-    void* out = g.C;
-    float* partial = st->at<float>(st->w.splitm);
-    const int Kz = g.K / ways;
-    char name[48];
-    snprintf(name, sizeof(name), "gemm_mfma256x256_%s_splitk", A_KM ? "TN" : (B_KM ? "NN" : "NT"));
-    {
-        ProfScope ps(st, name, 2.0 * g.M * (double)g.N * g.K, 0.0);
-        g.C = partial; g.K = Kz; g.epi = Epilogue(); g.epi.out_f32 = 1;
-        g.batch = ways; g.batch_inner = 1;
-        g.a_bo = (long)Kz * g.a_cs; g.b_bo = (long)Kz * g.b_rs; g.c_bo = (long)g.M * g.N;
-        if (!hip_ok(launch_tile<256, 256, A_KM, B_KM, 4>(st, g), name)) return AMDP_E_HIP;
+hipError_t launch_dl(amdp_stage* st, const GemmArgs& g, const DlPlan& p) {
+    switch (p.tile) {
+        case DL_256: return launch_gemm_mfma_dl<256, 256, A_KM, B_KM, 2, 2, 3, 2, 1>(g, st->launch, p.parts, p.k_part);
+        case DL_256x128: return launch_gemm_mfma_dl<256, 128, A_KM, B_KM, 4, 2, 3, 3, 1>(g, st->launch, p.parts, p.k_part);
+        case DL_128: return launch_gemm_mfma_dl<128, 128, A_KM, B_KM, 2, 4, 3, 3, 1>(g, st->launch, p.parts, p.k_part);
+        case DL_128_PAIR: return launch_gemm_mfma_dl<128, 128, A_KM, B_KM, 2, 2, 3, 2, 1>(g, st->launch, p.parts, p.k_part);
+        case DL_64_DEEP: return launch_gemm_mfma_dl<64, 64, A_KM, B_KM, 2, 2, 4, 4, 4>(g, st->launch, p.parts, p.k_part);
+        default: return launch_gemm_mfma_dl<64, 64, A_KM, B_KM, 2, 2, 2, 2, 4>(g, st->launch, p.parts, p.k_part);
     }
-    const long n8 = (long)g.M * g.N / 8;
-    ProfScope ps(st, "splitk_reduce", 0.0, (double)g.M * g.N * (4.0 * ways + 2.0 + (epi.res ? 2.0 : 0.0)));
-    hipLaunchKernelGGL(splitk_epilogue_kernel, dim3(direct_grid(n8, ACC_BLOCK)), dim3(ACC_BLOCK), 0, st->launch,
-                       (bf16*)out, partial, (const bf16*)epi.bias, (const bf16*)epi.res, n8, g.N, ways);
+}
+
+// The plan of a plain product, or the one its options force.
+DlPlan choose_dl(const amdp_stage* st, const GemmArgs& g, bool dw) {
+    const bool heavy = g.epi.out_f32 || g.epi.res || g.epi.gelu_u || g.epi.aux_out;
+    const bool may_split = !g.epi.gelu_u && !g.epi.aux_out && g.ldc == g.N && (!g.epi.res || g.epi.ldr == g.N) && g.epi.alpha == 1.0f;
+    const size_t scratch = dw ? st->w.splitk_bytes : st->w.splitm_bytes;
+    if (st->force_tile > 0) {
+        const long t128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128), t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+        return {st->force_tile == 256 ? DL_256 : st->force_tile == 128 ? (t128 > st->n_cu ? DL_128_PAIR : DL_128)
+                                               : (t64 > 2 * st->n_cu ? DL_64 : DL_64_DEEP), 1, g.K};
+    }
+    if (may_split && dw && st->splitk_min_k && g.M % 128 == 0 && g.N % 128 == 0) {
+        const long tiles = (long)(g.M / 128) * (g.N / 128);
+        int ways = 1;
+        while (ways < 8 && tiles * ways * 2 <= st->n_cu && g.K % (ways * 2 * MF_BK) == 0 && g.K / (ways * 2) >= st->splitk_min_k &&
+               (size_t)g.M * g.N * 4 * (size_t)(ways * 2) <= scratch)
+            ways *= 2;
+        if (ways > 1) return {DL_128, ways, g.K / ways};
+    }
+    if (may_split && !dw && st->split_main_min_k && g.M % 256 == 0 && g.N % 256 == 0 && g.K % (2 * MF_BK) == 0 &&
+        g.K / 2 >= st->split_main_min_k && (long)(g.M / 256) * (g.N / 256) * 2 <= st->n_cu && (size_t)g.M * g.N * 4 * 2 <= scratch)
+        return {DL_256, 2, g.K / 2};
+    return dl_plan(g.M, g.N, g.K, heavy, may_split && !(dw ? st->splitk_min_k : st->split_main_min_k), scratch, st->n_cu);
+}
+
+template <bool A_KM, bool B_KM>
+int gemm_bf16_layout(amdp_stage* st, const GemmArgs& g) {
+    const bool square = st->force_tile == 0 || st->force_tile == 256 || st->force_tile == 128 || st->force_tile == 64;
+    if (!st->use_direct || !square || !mfma_dl_shape_ok(g, A_KM, B_KM)) return gemm_bf16_staged<A_KM, B_KM>(st, g);
+    const DlPlan p = choose_dl(st, g, A_KM);
+    char name[48];
+    snprintf(name, sizeof(name), "gemm_mfma%dx%d_%s%s", DL_MODEL[p.tile].bm, DL_MODEL[p.tile].bn, A_KM ? "TN" : (B_KM ? "NN" : "NT"),
+             p.parts > 1 ? "_splitk" : "");
+    if (p.parts == 1) {
+        ProfScope ps(st, name, gemm_flops(g), 0.0);
+        return hip_ok(launch_dl<A_KM, B_KM>(st, g, p), name) ? AMDP_OK : AMDP_E_HIP;
+    }
+    float* partial = st->at<float>(A_KM ? st->w.splitk : st->w.splitm);
+    {
+        ProfScope ps(st, name, gemm_flops(g), 0.0);
+        GemmArgs part = g;
+        part.C = partial; part.epi = Epilogue(); part.epi.out_f32 = 1; part.c_bo = (long)g.M * g.N;
+        if (!hip_ok(launch_dl<A_KM, B_KM>(st, part, p), name)) return AMDP_E_HIP;
+    }
+    ProfScope ps(st, "splitk_reduce", 0.0, (double)g.M * g.N * (4.0 * p.parts + (g.epi.out_f32 ? 4.0 : 2.0) + (g.epi.accumulate ? 4.0 : g.epi.res ? 2.0 : 0.0)));
+    if (g.epi.out_f32) {
+        const long n4 = (long)g.M * g.N / 4;
+        hipLaunchKernelGGL(splitk_reduce_kernel, dim3(direct_grid(n4, ACC_BLOCK)), dim3(ACC_BLOCK), 0, st->launch, (float*)g.C, partial,
+                           n4, p.parts, g.epi.accumulate);
+    } else {
+        const long n8 = (long)g.M * g.N / 8;
+        hipLaunchKernelGGL(splitk_epilogue_kernel, dim3(direct_grid(n8, ACC_BLOCK)), dim3(ACC_BLOCK), 0, st->launch, (bf16*)g.C, partial,
+                           (const bf16*)g.epi.bias, (const bf16*)g.epi.res, n8, g.N, p.parts);
+    }
     return after_launch();
 }
+
+enum GemmLayout { G_NN, G_NT, G_TN };
 
 // lda/ldb are the leading dimensions of the operands AS STORED:
 //   NN: A [M,K] lda, B [K,N] ldb      NT: A [M,K], B [N,K]      TN: A [K,M], B [K,N]
@@ -497,12 +514,8 @@ int gemm(amdp_stage* st, GemmLayout lay, GemmArgs g, long lda, long ldb) {
         return hip_ok(launch_gemm_simple<float>(g, st->launch), "gemm_generic_fp32") ? AMDP_OK : AMDP_E_HIP;
     }
     switch (lay) {
-        case G_NN:
-            if (const int ways = main_split(st, g, false, true); ways > 1) return gemm_main_split<false, true>(st, g, ways);
-            return gemm_bf16_layout<false, true>(st, g);
-        case G_NT:
-            if (const int ways = main_split(st, g, false, false); ways > 1) return gemm_main_split<false, false>(st, g, ways);
-            return gemm_bf16_layout<false, false>(st, g);
+        case G_NN: return gemm_bf16_layout<false, true>(st, g);
+        case G_NT: return gemm_bf16_layout<false, false>(st, g);
         default: return gemm_bf16_layout<true, true>(st, g);
     }
 }
@@ -843,52 +856,13 @@ int linear_dx(amdp_stage* st, const void* dY, const void* W, const void* gelu_u,
     g.epi.gelu_u = gelu_u; g.epi.ldu = K; g.epi.res = res; g.epi.ldr = K;
     return gemm(st, G_NT, g, N, N);
 }
-// How many ways the token dimension of a weight-gradient product [rows x cols] is
-// split over workgroups (1 = not at all). A product whose 128x128 tiles cover at
-// most half of the compute units gets one workgroup per unit instead: the parts
-// go to scratch and are added in fixed order afterwards (no float atomics).
-int dw_split(const amdp_stage* st, int rows, int cols, int tokens) {
-    if (!st->d.bf || st->force_tile != 0 || rows % 128 || cols % 128 || !st->w.splitk_bytes) return 1;
-    const long tiles = (long)(rows / 128) * (cols / 128);
-    int ways = 1;
-    while (ways < 8 && tiles * ways * 2 <= st->n_cu && tokens % (ways * 2 * MF_BK) == 0 &&
-           tokens / (ways * 2) >= st->splitk_min_k &&
-           (size_t)rows * cols * 4 * (size_t)(ways * 2) <= st->w.splitk_bytes)
-        ways *= 2;
-    return ways;
-}
 // dW[K,N] (fp32) = X[M,K]^T dY[M,N]
 int linear_dw(amdp_stage* st, const void* X, const void* dY, float* dW, int M, int N, int K) {
     GemmArgs g{};
     g.A = X; g.B = dY; g.C = dW; g.M = K; g.N = N; g.K = M; g.ldc = N;
     g.epi.out_f32 = 1;
     g.epi.accumulate = st->fused_acc ? 1 : 0;
-    const int ways = dw_split(st, K, N, M);
-    if (ways == 1) return gemm(st, G_TN, g, K, N);
-    // one batched launch: part z contracts tokens [z * M/ways, (z+1) * M/ways) into partial[z]
-    float* partial = st->at<float>(st->w.splitk);
-    const int Mz = M / ways;
-    g.C = partial; g.K = Mz; g.epi.accumulate = 0;
-    g.batch = ways; g.batch_inner = 1;
-    g.a_rs = 1; g.a_cs = K; g.b_rs = N; g.b_cs = 1;
-    g.a_bo = (long)Mz * K; g.b_bo = (long)Mz * N; g.c_bo = (long)K * N;
-    if (!mfma_shape_ok<128, 128>(g, true, true)) {      // alignment the tile kernel needs: fall back to one launch
-        GemmArgs one{};
-        one.A = X; one.B = dY; one.C = dW; one.M = K; one.N = N; one.K = M; one.ldc = N;
-        one.epi.out_f32 = 1; one.epi.accumulate = st->fused_acc ? 1 : 0;
-        return gemm(st, G_TN, one, K, N);
-    }
-    {
-        ProfScope ps(st, "gemm_mfma128x128_TN_splitk", 2.0 * K * (double)N * M, 0.0);
-        hipError_t e = st->use_tr ? launch_gemm_mfma_inst<128, 128, true, true, true, 4>(g, st->launch)
-                                  : launch_gemm_mfma_inst<128, 128, true, true, false, 4>(g, st->launch);
-        if (!hip_ok(e, "gemm_mfma128x128_TN_splitk")) return AMDP_E_HIP;
-    }
-    const long n4 = (long)K * N / 4;
-    ProfScope ps(st, "splitk_reduce", 0.0, (double)K * N * 4 * (ways + 1 + (st->fused_acc ? 1 : 0)));
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(direct_grid(n4, ACC_BLOCK)), dim3(ACC_BLOCK), 0, st->launch, dW,
-                       partial, n4, ways, st->fused_acc ? 1 : 0);
-    return after_launch();
+    return gemm(st, G_TN, g, K, N);
 }
 
 template <class T>
