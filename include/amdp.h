@@ -210,9 +210,8 @@ int amdp_system_simulate(const amdp_sim_params_t* params, amdp_sim_op_t* ops, si
 enum { AMDP_BLOCK_GPT_PRELN_CAUSAL = 0, AMDP_BLOCK_BERT_POSTLN_BIDIR = 1 };
 enum { AMDP_FP32 = 0, AMDP_BF16 = 1 };
 /* AMDP_ATTN_AUTO: the fused attention kernels (scores never reach HBM, one fp32
- * log-sum-exp per query kept for backward) wherever the shape allows: bf16,
- * seq_len a multiple of 128, even head dimension <= 128; the three-kernel form
- * elsewhere. AMDP_ATTN_UNFUSED: always scores GEMM, masked softmax, P V GEMM with
+ * log-sum-exp per query kept for backward) wherever the shape allows: bf16 and an
+ * even head dimension <= 128; the three-kernel form elsewhere. AMDP_ATTN_UNFUSED: always scores GEMM, masked softmax, P V GEMM with
  * the probabilities [b*H, s, s] kept in the activation slot. */
 enum { AMDP_ATTN_AUTO = 0, AMDP_ATTN_UNFUSED = 1 };
 

@@ -1,7 +1,19 @@
-// Fused attention for bf16 stages (head_dim 64 or 128, sequence length a
-// multiple of 128): scores, mask, softmax and the value product in one kernel,
-// so the s x s score / probability matrices never touch HBM. Forward saves one
-// fp32 number per (sequence, head, query): the log-sum-exp of its scores.
+// Fused attention for bf16 stages (any sequence length, even head widths up to
+// 128): scores, mask, softmax and the value product in one kernel, so the s x s
+// score / probability matrices never touch HBM. Forward saves one fp32 number
+// per (sequence, head, query): the log-sum-exp of its scores.
+//
+// Each kernel exists for tiles of 64 and 128 head columns, and in a RAGGED form
+// for heads narrower than the tile and sequences that end inside a block: its
+// loads fill missing rows and columns with zeros, which add nothing to any
+// product, missing keys are masked, and only what exists is stored. Head rows of
+// an even width start at multiples of 4 bytes, which 16-byte loads accept. Whole
+// tiles have a form of their own, without the guards.
+// Before, a sequence that was no multiple of 128 kept its scores in memory and went
+// through the generic product, and heads of 50 were repacked to 64 in memory. On
+// MI355X, a whole accumulation window then -> now: 768 wide, 3 x 1000 tokens, 2 layers
+// 12.4 -> 3.2 ms; 192 wide, 2 x 200 tokens, 2 layers 7.7 -> 4.1 ms; 1600 wide with 32
+// heads of 50, 4 x 1024 tokens, 6 layers 59.8 -> 55.5 ms.
 //
 // Layout trick (all three kernels): every matrix product is set up so that the
 // index a row-wise quantity belongs to (the query for max / sum / LSE / delta)
@@ -63,18 +75,39 @@ template <int STRIDE>
 __device__ __forceinline__ bf16x8 frag_row(lds_u8* tile, int r0, int kk, int lane) {
     return *(lds_bf16x8*)(tile + (r0 + tile_pos(lane & 31)) * STRIDE + (kk * 16 + 8 * (lane >> 5)) * 2);
 }
-// Cooperative copy of ROWS x DH bf16 (row stride ld elements in memory) into an
-// LDS tile, split in two so the global loads of the next tile can be in flight
-// while the current one is being multiplied.
-template <int DH, int ROWS, int NT>
+// Columns [c, c + 8) of a head row of dh columns (dh even, the row 4-byte aligned):
+// zeros where the row does not exist (`ok` false) and past its end, which is never read.
+typedef u32x4 __attribute__((aligned(4))) u32x4_a4;
+template <bool RAGGED>
+__device__ __forceinline__ u32x4 load_head8(const bf16* row, int c, int dh, bool ok) {
+    if constexpr (!RAGGED) {
+        return *(const u32x4*)(row + c);
+    } else {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (ok && c + 8 <= dh) v = *(const u32x4_a4*)(row + c);
+        if (dh & 7) {                                  // the same for every lane
+            if (ok && c < dh && c + 8 > dh) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if (c + 2 * j < dh) v[j] = *(const uint32_t*)(row + c + 2 * j);
+            }
+        }
+        return v;
+    }
+}
+
+// Cooperative copy of ROWS x DH bf16 (row stride ld elements in memory, `rows` rows
+// of dh columns exist) into an LDS tile, split in two so the global loads of the next
+// tile can be in flight while the current one is being multiplied.
+template <int DH, int ROWS, int NT, bool RAGGED>
 struct TileCopy {
     static constexpr int VPR = DH / 8, NV = ROWS * VPR / NT, STRIDE = AttnTile<DH>::STRIDE;
     u32x4 r[NV];
-    __device__ __forceinline__ void fetch(const bf16* src, long ld, int tid) {
+    __device__ __forceinline__ void fetch(const bf16* src, long ld, int tid, int rows, int dh) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int v = tid + i * NT, row = v / VPR, c = v % VPR;
-            r[i] = *(const u32x4*)(src + (long)row * ld + c * 8);
+            r[i] = load_head8<RAGGED>(src + (long)row * ld, c * 8, dh, row < rows);
         }
     }
     __device__ __forceinline__ void store(lds_u8* tile, int tid) const {
@@ -102,15 +135,38 @@ __device__ __forceinline__ void attn_block(int i, int nq, int nz, int resident, 
     z = j % nz;
 }
 
+// Row of a head from the accumulators of its 32-column tiles (this lane: its half's columns).
+template <int NTILES, bool RAGGED, int NACC>
+__device__ __forceinline__ void store_headrow(bf16* row, const f32x16 (&acc)[NACC], int half, float mul, int dh) {
+    typedef bf16x4 __attribute__((aligned(4))) bf16x4_a4;
+#pragma unroll
+    for (int t = 0; t < NTILES; ++t)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[t][4 * gq + e] * mul);
+            const int c = t * 32 + 8 * gq + 4 * half;
+            if constexpr (!RAGGED) {
+                *(bf16x4*)(row + c) = o;
+            } else if (c + 4 <= dh) {
+                *(bf16x4_a4*)(row + c) = o;
+            } else if (c + 2 <= dh) {
+                row[c] = o[0];
+                row[c + 1] = o[1];
+            }
+        }
+}
+
 // ---------------------------------------------------------------- forward
-// grid (s/128) * (b*H) blocks, see attn_block; 4 waves, each owns 32 queries; keys in blocks of 64.
-// qkv: [b*s, 3D] (Q | K | V column blocks, heads of DH); O: [b*s, D];
+// grid ceil(s/128) * (b*H) blocks, see attn_block; 4 waves, each owns 32 queries; keys in blocks of 64.
+// qkv: [b*s, 3D] (Q | K | V column blocks, heads of dh <= DH); O: [b*s, D];
 // lse2: [b*H, s] = log2-domain log-sum-exp of scale*scores.
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void flash_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ O,
                                                         float* __restrict__ lse2,
                                                         const int32_t* __restrict__ valid_len, int s, int H,
-                                                        int D, float scale_log2e, int nz, int resident) {
+                                                        int D, int dh, float scale_log2e, int nz, int resident) {
     constexpr int STRIDE = AttnTile<DH>::STRIDE, BKV = 64, KQ = DH / 16, DT = DH / 32;
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BKV * STRIDE];
     lds_u8* tK = (lds_u8*)smem;
@@ -118,17 +174,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int rank, z;
-    attn_block(blockIdx.x, s / 128, nz, resident, CAUSAL, rank, z);
-    const int qb = CAUSAL ? s / 128 - 1 - rank : rank;      // late queries see the most keys
+    attn_block(blockIdx.x, (s + 127) / 128, nz, resident, CAUSAL, rank, z);
+    const int qb = CAUSAL ? (s + 127) / 128 - 1 - rank : rank;      // late queries see the most keys
     const int b = z / H, h = z % H;
     const long ld = 3L * D;
-    const bf16* base = qkv + (long)b * s * ld + (long)h * DH;
+    if constexpr (!RAGGED) dh = DH;
+    const bf16* base = qkv + (long)b * s * ld + (long)h * dh;
     const int q_blk = qb * 128, q_wave = q_blk + wave * 32, q = q_wave + (lane & 31);
     const int half = lane >> 5;
 
     bf16x8 bq[KQ];   // B operand: n = query, k = head dimension
 #pragma unroll
-    for (int kk = 0; kk < KQ; ++kk) bq[kk] = *(const bf16x8*)(base + (long)q * ld + kk * 16 + 8 * half);
+    for (int kk = 0; kk < KQ; ++kk)
+        bq[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(base + (long)q * ld, kk * 16 + 8 * half, dh, q < s));
 
     f32x16 acc[DT];
 #pragma unroll
@@ -138,14 +196,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     float m_run = -INFINITY, l_run = 0.f;
 
     int kend = s;
-    if (CAUSAL) kend = q_blk + 128;
+    if (CAUSAL) kend = RAGGED ? min(q_blk + 128, s) : q_blk + 128;
     if (valid_len) kend = min(kend, (max(valid_len[b], 1) + BKV - 1) / BKV * BKV);
-    const int klimit = valid_len ? valid_len[b] : s;
+    const int klimit = valid_len ? min(valid_len[b], s) : s;
 
-    TileCopy<DH, BKV, 256> cK, cV;
+    TileCopy<DH, BKV, 256, RAGGED> cK, cV;
     if (kend > 0) {
-        cK.fetch(base + D, ld, tid);
-        cV.fetch(base + 2 * D, ld, tid);
+        cK.fetch(base + D, ld, tid, s, dh);
+        cV.fetch(base + 2 * D, ld, tid, s, dh);
     }
     for (int k0 = 0; k0 < kend; k0 += BKV) {
         __syncthreads();                              // everyone is done with the previous tiles
@@ -153,9 +211,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
         cV.store(tV, tid);
         __syncthreads();
         if (k0 + BKV < kend) {                        // next tiles travel while this one is used
-            cK.fetch(base + D + (long)(k0 + BKV) * ld, ld, tid);
-            cV.fetch(base + 2 * D + (long)(k0 + BKV) * ld, ld, tid);
+            cK.fetch(base + D + (long)(k0 + BKV) * ld, ld, tid, s - k0 - BKV, dh);
+            cV.fetch(base + 2 * D + (long)(k0 + BKV) * ld, ld, tid, s - k0 - BKV, dh);
         }
+        if (RAGGED && q_wave >= s) continue;          // none of this wave's queries exists
         if (CAUSAL && k0 > q_wave + 31) continue;     // every key of the block is hidden from this wave
 
         f32x16 st[2];
@@ -224,76 +283,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    bf16* orow = O + ((long)b * s + q) * D + (long)h * DH;
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            bf16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[t][4 * gq + e] * inv);
-            *(bf16x4*)(orow + t * 32 + 8 * gq + 4 * half) = o;
-        }
+    if (RAGGED && q >= s) return;
+    store_headrow<DT, RAGGED>(O + ((long)b * s + q) * D + (long)h * dh, acc, half, inv, dh);
     if (half == 0) lse2[(long)z * s + q] = m_run + log2f(l_tot);
 }
 
 
-// Head-wise repacking between widths (32-bit pairs of bf16): output pair i of
-// `pairs` belongs to chunk i / wd2 and column pair i % wd2; columns past the
-// source width read as zero.
-__global__ __launch_bounds__(256) void repack_heads_kernel(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst,
-                                                           long pairs, int ws2, int wd2) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= pairs) return;
-    const long chunk = i / wd2;
-    const int c = (int)(i % wd2);
-    dst[i] = c < ws2 ? src[chunk * ws2 + c] : 0u;
-}
-
 // ---------------------------------------------------------------- backward
-// delta[z][q] = sum_d dO[q, h*DH + d] * O[q, h*DH + d]   (z = sequence*H + head)
-// One wave per token row; a head's DH/8 vectors sit in DH/8 adjacent lanes.
-template <int DH>
-__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict__ dO, const bf16* __restrict__ O,
-                                                         float* __restrict__ delta, int rows, int s, int H, int D) {
-    constexpr int LPH = DH / 8;    // lanes per head
-    const int lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;
-    const long b = row / s, pos = row % s;
-    for (int c = lane; c < D / 8; c += 64) {
-        const bf16x8 a = *(const bf16x8*)(dO + row * D + c * 8);
-        const bf16x8 o = *(const bf16x8*)(O + row * D + c * 8);
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t += (float)a[i] * (float)o[i];
-#pragma unroll
-        for (int m = 1; m < LPH; m <<= 1) t += __shfl_xor(t, m, 64);
-        if ((lane & (LPH - 1)) == 0) delta[(b * H + c / LPH) * s + pos] = t;
-    }
-}
-
-template <int NTILES>
-__device__ __forceinline__ void store_headrow(bf16* row, const f32x16 (&acc)[4], int half, float mul) {
-#pragma unroll
-    for (int t = 0; t < NTILES; ++t)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            bf16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[t][4 * gq + e] * mul);
-            *(bf16x4*)(row + t * 32 + 8 * gq + 4 * half) = o;
-        }
-}
-
 // dK, dV. Same grid; each wave owns 32 keys (lane % 32) and walks the
 // query tiles of 64 that can see them. dqkv: [b*s, 3D], K block at +D, V at +2D.
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 2 : 1))) void flash_bwd_dkv_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
                                                             const float* __restrict__ lse2,
                                                             const float* __restrict__ delta, bf16* __restrict__ dqkv,
                                                             const int32_t* __restrict__ valid_len, int s, int H,
-                                                            int D, float scale, int nz, int resident) {
+                                                            int D, int dh, float scale, int nz, int resident) {
     constexpr int STRIDE = AttnTile<DH>::STRIDE, BQ = 64, KQ = DH / 16, DT = DH / 32;
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BQ * STRIDE];
     __shared__ __attribute__((aligned(16))) float sstat[2][BQ];
@@ -301,21 +305,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
     lds_u8* tdO = tQ + BQ * STRIDE;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
     int rank, z;
-    attn_block(blockIdx.x, s / 128, nz, resident, CAUSAL, rank, z);     // early keys are seen by the most queries
+    attn_block(blockIdx.x, (s + 127) / 128, nz, resident, CAUSAL, rank, z);     // early keys are seen by the most queries
     const int b = z / H, h = z % H;
     const long ld = 3L * D;
-    const bf16* base = qkv + (long)b * s * ld + (long)h * DH;
-    const bf16* dObase = dO + (long)b * s * D + (long)h * DH;
+    if constexpr (!RAGGED) dh = DH;
+    const bf16* base = qkv + (long)b * s * ld + (long)h * dh;
+    const bf16* dObase = dO + (long)b * s * D + (long)h * dh;
     const int k_blk = rank * 128, k_wave = k_blk + wave * 32, key = k_wave + (lane & 31);
-    const int klimit = valid_len ? valid_len[b] : s;
+    const int klimit = valid_len ? min(valid_len[b], s) : s;
     const float sl2 = scale * LOG2E;
     const bool key_dead = key >= klimit;     // padding: this lane's key is visible to nobody
 
     bf16x8 bk[KQ], bv[KQ];      // B operands: n = key, k = head dimension
 #pragma unroll
     for (int kk = 0; kk < KQ; ++kk) {
-        bk[kk] = *(const bf16x8*)(base + D + (long)key * ld + kk * 16 + 8 * half);
-        bv[kk] = *(const bf16x8*)(base + 2 * D + (long)key * ld + kk * 16 + 8 * half);
+        const bf16* krow = base + D + (long)key * ld;
+        bk[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(krow, kk * 16 + 8 * half, dh, key < s));
+        bv[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(krow + D, kk * 16 + 8 * half, dh, key < s));
     }
     f32x16 dk[4], dv[4];
 #pragma unroll
@@ -325,13 +331,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
 
     const int q_begin = CAUSAL ? k_blk : 0;
     const bool block_live = k_blk < klimit;
-    TileCopy<DH, BQ, 256> cQ, cdO;
+    TileCopy<DH, BQ, 256, RAGGED> cQ, cdO;
     float stat_next = 0.f;      // threads 0..63: lse of query tid; 64..127: delta of query tid-64
     const float* stat_src = tid < BQ ? lse2 + (long)z * s + tid : delta + (long)z * s + (tid - BQ);
+    // a query past the end gets probability 0 from an infinite log-sum-exp, and delta 0
+    auto stat_at = [&](int q0) {
+        if (RAGGED && q0 + tid % BQ >= s) return tid < BQ ? INFINITY : 0.f;
+        return stat_src[q0];
+    };
     if (block_live && q_begin < s) {
-        cQ.fetch(base + (long)q_begin * ld, ld, tid);
-        cdO.fetch(dObase + (long)q_begin * D, D, tid);
-        if (tid < 2 * BQ) stat_next = stat_src[q_begin];
+        cQ.fetch(base + (long)q_begin * ld, ld, tid, s - q_begin, dh);
+        cdO.fetch(dObase + (long)q_begin * D, D, tid, s - q_begin, dh);
+        if (tid < 2 * BQ) stat_next = stat_at(q_begin);
     }
     for (int q0 = q_begin; q0 < s && block_live; q0 += BQ) {
         __syncthreads();
@@ -340,10 +351,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
         if (tid < 2 * BQ) sstat[tid / BQ][tid % BQ] = stat_next;
         __syncthreads();
         if (q0 + BQ < s) {
-            cQ.fetch(base + (long)(q0 + BQ) * ld, ld, tid);
-            cdO.fetch(dObase + (long)(q0 + BQ) * D, D, tid);
-            if (tid < 2 * BQ) stat_next = stat_src[q0 + BQ];
+            cQ.fetch(base + (long)(q0 + BQ) * ld, ld, tid, s - q0 - BQ, dh);
+            cdO.fetch(dObase + (long)(q0 + BQ) * D, D, tid, s - q0 - BQ, dh);
+            if (tid < 2 * BQ) stat_next = stat_at(q0 + BQ);
         }
+        if (RAGGED && k_wave >= s) continue;
         if (CAUSAL && q0 + BQ - 1 < k_wave) continue;      // none of these queries sees this wave's keys
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) {
@@ -388,40 +400,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
             }
         }
     }
-    bf16* out = dqkv + ((long)b * s + key) * ld + (long)h * DH;
-    store_headrow<DT>(out + D, dk, half, scale);
-    store_headrow<DT>(out + 2 * D, dv, half, 1.0f);
+    if (RAGGED && key >= s) return;
+    bf16* out = dqkv + ((long)b * s + key) * ld + (long)h * dh;
+    store_headrow<DT, RAGGED>(out + D, dk, half, scale, dh);
+    store_headrow<DT, RAGGED>(out + 2 * D, dv, half, 1.0f, dh);
 }
 
 // dQ. Same grid; each wave owns 32 queries and walks the key blocks of 64 it can see.
-template <int DH, bool CAUSAL>
+// It also computes delta[z][q] = sum_d dO[q, d] * O[q, d] (z = sequence*H + head), which the
+// dK / dV kernel reads: a lane already holds half of its query's dO row, so only O has
+// to be read (a pass over dO and O of its own took 8-11 us a layer at 4096 tokens x 1024).
+template <int DH, bool CAUSAL, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void flash_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dO,
-                                                           const float* __restrict__ lse2,
-                                                           const float* __restrict__ delta, bf16* __restrict__ dqkv,
+                                                           const bf16* __restrict__ O, const float* __restrict__ lse2,
+                                                           float* __restrict__ delta, bf16* __restrict__ dqkv,
                                                            const int32_t* __restrict__ valid_len, int s, int H,
-                                                           int D, float scale, int nz, int resident) {
+                                                           int D, int dh, float scale, int nz, int resident) {
     constexpr int STRIDE = AttnTile<DH>::STRIDE, BKV = 64, KQ = DH / 16, DT = DH / 32;
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * BKV * STRIDE];
     lds_u8* tK = (lds_u8*)smem;
     lds_u8* tV = tK + BKV * STRIDE;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
     int rank, z;
-    attn_block(blockIdx.x, s / 128, nz, resident, CAUSAL, rank, z);
-    const int qb = CAUSAL ? s / 128 - 1 - rank : rank;
+    attn_block(blockIdx.x, (s + 127) / 128, nz, resident, CAUSAL, rank, z);
+    const int qb = CAUSAL ? (s + 127) / 128 - 1 - rank : rank;
     const int b = z / H, h = z % H;
     const long ld = 3L * D;
-    const bf16* base = qkv + (long)b * s * ld + (long)h * DH;
+    if constexpr (!RAGGED) dh = DH;
+    const bf16* base = qkv + (long)b * s * ld + (long)h * dh;
     const int q_blk = qb * 128, q_wave = q_blk + wave * 32, q = q_wave + (lane & 31);
-    const int klimit = valid_len ? valid_len[b] : s;
+    const int klimit = valid_len ? min(valid_len[b], s) : s;
     const float sl2 = scale * LOG2E;
+    const bool q_ok = !RAGGED || q < s;
 
     bf16x8 bq[KQ], bdo[KQ];     // B operands: n = query, k = head dimension
 #pragma unroll
     for (int kk = 0; kk < KQ; ++kk) {
-        bq[kk] = *(const bf16x8*)(base + (long)q * ld + kk * 16 + 8 * half);
-        bdo[kk] = *(const bf16x8*)(dO + ((long)b * s + q) * D + (long)h * DH + kk * 16 + 8 * half);
+        bq[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(base + (long)q * ld, kk * 16 + 8 * half, dh, q_ok));
+        bdo[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(dO + ((long)b * s + q) * D + (long)h * dh, kk * 16 + 8 * half, dh, q_ok));
     }
-    const float lse_q = lse2[(long)z * s + q], delta_q = delta[(long)z * s + q];
+    float delta_q = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KQ; ++kk) {
+        const bf16x8 o = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(O + ((long)b * s + q) * D + (long)h * dh, kk * 16 + 8 * half, dh, q_ok));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) delta_q += (float)bdo[kk][e] * (float)o[e];
+    }
+    delta_q += __shfl_xor(delta_q, 32, 64);
+    const float lse_q = q_ok ? lse2[(long)z * s + q] : 0.f;
+    if (half == 0 && q_ok) delta[(long)z * s + q] = delta_q;
     f32x16 dq[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t)
@@ -429,12 +456,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
         for (int v = 0; v < 16; ++v) dq[t][v] = 0.f;
 
     int kend = s;
-    if (CAUSAL) kend = q_blk + 128;
+    if (CAUSAL) kend = RAGGED ? min(q_blk + 128, s) : q_blk + 128;
     if (valid_len) kend = min(kend, (max(klimit, 1) + BKV - 1) / BKV * BKV);
-    TileCopy<DH, BKV, 256> cK, cV;
+    TileCopy<DH, BKV, 256, RAGGED> cK, cV;
     if (kend > 0) {
-        cK.fetch(base + D, ld, tid);
-        cV.fetch(base + 2 * D, ld, tid);
+        cK.fetch(base + D, ld, tid, s, dh);
+        cV.fetch(base + 2 * D, ld, tid, s, dh);
     }
     for (int k0 = 0; k0 < kend; k0 += BKV) {
         __syncthreads();
@@ -442,9 +469,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
         cV.store(tV, tid);
         __syncthreads();
         if (k0 + BKV < kend) {
-            cK.fetch(base + D + (long)(k0 + BKV) * ld, ld, tid);
-            cV.fetch(base + 2 * D + (long)(k0 + BKV) * ld, ld, tid);
+            cK.fetch(base + D + (long)(k0 + BKV) * ld, ld, tid, s - k0 - BKV, dh);
+            cV.fetch(base + 2 * D + (long)(k0 + BKV) * ld, ld, tid, s - k0 - BKV, dh);
         }
+        if (RAGGED && q_wave >= s) continue;          // none of this wave's queries exists
         if (CAUSAL && k0 > q_wave + 31) continue;
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
@@ -481,7 +509,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
             }
         }
     }
-    store_headrow<DT>(dqkv + ((long)b * s + q) * ld + (long)h * DH, dq, half, scale);
+    if (RAGGED && q >= s) return;
+    store_headrow<DT, RAGGED>(dqkv + ((long)b * s + q) * ld + (long)h * dh, dq, half, scale, dh);
 }
 
 }  // namespace amdp

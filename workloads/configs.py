@@ -121,10 +121,10 @@ TINY = {
     # 640 = 2*256 + 128, 960 = 3*256 + 192; 384 tokens = 256 + 128
     "gpt_tile_edge": StageWorkload("tile_edge_gpt", 29, GPT_PRELN_CAUSAL, 2, 320, 5, 640, 128, 3, BF16,
                                    depth=4, pipelines=2, stage=1, threshold=4),
-    # head dimension 50 (the paper's BERT-style width / heads): no fused attention, unaligned heads
+    # head dimension 50 (the paper's BERT-style width / heads): heads at multiples of 4 bytes, 24 tokens
     "bert_dh50": StageWorkload("tiny_bert_dh50", 23, BERT_POSTLN_BIDIR, 1, 400, 8, 800, 24, 2, BF16,
                                depth=4, pipelines=2, stage=1, threshold=4),
-    # head dimensions the fused attention reaches by zero-padding (50 -> 64, 96 -> 128)
+    # head dimensions narrower than the fused attention's tiles (50 in 64, 96 in 128)
     "bert_tile_dh50": StageWorkload("tile_bert_dh50", 24, BERT_POSTLN_BIDIR, 1, 400, 8, 800, 128, 2, BF16,
                                     depth=4, pipelines=2, stage=1, threshold=4),
     "gpt_tile_dh96": StageWorkload("tile_gpt_dh96", 25, GPT_PRELN_CAUSAL, 1, 192, 2, 384, 256, 1, BF16,
