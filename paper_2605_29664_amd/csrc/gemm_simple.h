@@ -1,6 +1,6 @@
 // Generic fully-guarded GEMM: any shape, any strides, fp32 FMA arithmetic.
-// Used for the fp32 stage configuration and for bf16 shapes that are not
-// multiples of the MFMA kernel's tiles.
+// Used for the batched bf16 products of the attention form with its scores in
+// memory whose shapes are not multiples of the register-staged kernel's tiles.
 #pragma once
 #include "common.h"
 

@@ -7,6 +7,7 @@
 #include "attention.h"
 #include "embedding.h"
 #include "common.h"
+#include "gemm_fp32.h"
 #include "gemm_mfma.h"
 #include "gemm_mfma_dl.h"
 #include "gemm_plan.h"
@@ -503,8 +504,8 @@ int gemm(amdp_stage* st, GemmLayout lay, GemmArgs g, long lda, long ldb) {
     }
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return AMDP_OK;
     if (!st->d.bf) {
-        ProfScope ps(st, "gemm_generic_fp32", gemm_flops(g), 0.0);
-        return hip_ok(launch_gemm_simple<float>(g, st->launch), "gemm_generic_fp32") ? AMDP_OK : AMDP_E_HIP;
+        ProfScope ps(st, "gemm_mfma_fp32", gemm_flops(g), 0.0);
+        return hip_ok(launch_gemm_fp32(g, st->n_cu, st->launch), "gemm_mfma_fp32") ? AMDP_OK : AMDP_E_HIP;
     }
     switch (lay) {
         case G_NN: return gemm_bf16_layout<false, true>(st, g);
