@@ -25,6 +25,20 @@
 // 16-wide k-step and 8..15 as the second fixes a permutation of the keys, and
 // the A operand (V^T, read from the [key][dh] LDS tile with the transposing
 // read, 4 consecutive keys per read) is fetched in the same permuted order.
+//
+// What bounds them: per 32x32 tile of scores and wave a kernel spends 256 to 512 cycles
+// of matrix instructions and as many of vector instructions (an exponential costs four
+// others); the rest of a step is latency. So the fragments a product needs are read from
+// LDS together, ahead of it and behind a scheduling fence: the value fragments before the
+// softmax, the transposed ones of the backward before the exponentials. Left to the
+// compiler every pair of matrix instructions waited for its own reads. The backward
+// kernels' accumulators start at -lse and -delta instead of zero, which leaves two vector
+// instructions per score besides the exponential and the packing. Kernel times without
+// other work, before -> now (forward, dQ, dK/dV in us): 16 heads of 64, 4 x 1024 tokens,
+// causal 26.0 / 30.4 / 38.7 -> 25.5 / 28.8 / 34.7; 32 heads of 64, 2 x 2048, causal
+// 59.9 / 78.5 / 102 -> 57.4 / 73.1 / 91.6; 32 heads of 128, 2048, causal 65.9 / 95.5 / 144
+// -> 62.4 / 91.4 / 126. With the exponentials taken out the second case takes 43 / 60 / 72,
+// with the tile loads taken out 52 / 68 / 87.
 #pragma once
 #include "common.h"
 #include "gemm_mfma.h"
@@ -59,6 +73,9 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& p, int first) {
 
 // A-operand fragment (rows = 32 consecutive columns c0.. of the tile, k = the
 // permuted 16 keys of k-step `ks` inside the 32-row group starting at row r0).
+// Nothing is moved across it by the compiler's scheduler.
+__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
+
 template <int STRIDE>
 __device__ __forceinline__ bf16x8 frag_tr(lds_u8* tile, int r0, int ks, int c0, int lane) {
     // rows 16ks + 4h + j (h = lane / 32, j = 0..3) sit at positions 16ks + 4j + h,
@@ -94,6 +111,14 @@ __device__ __forceinline__ u32x4 load_head8(const bf16* row, int c, int dh, bool
         }
         return v;
     }
+}
+
+// A fragment that stays in registers over a kernel's whole loop: waits for its load here.
+// Left to its first use inside the loop, the wait there (memory counters complete in
+// order) is one for every load before that use, each step's prefetch among them.
+__device__ __forceinline__ bf16x8 arrived(u32x4 v) {
+    asm volatile("" : "+v"(v));
+    return __builtin_bit_cast(bf16x8, v);
 }
 
 // Cooperative copy of ROWS x DH bf16 (row stride ld elements in memory, `rows` rows
@@ -184,9 +209,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     const int half = lane >> 5;
 
     bf16x8 bq[KQ];   // B operand: n = query, k = head dimension
+    {
+        u32x4 raw[KQ];
 #pragma unroll
-    for (int kk = 0; kk < KQ; ++kk)
-        bq[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(base + (long)q * ld, kk * 16 + 8 * half, dh, q < s));
+        for (int kk = 0; kk < KQ; ++kk) raw[kk] = load_head8<RAGGED>(base + (long)q * ld, kk * 16 + 8 * half, dh, q < s);
+#pragma unroll
+        for (int kk = 0; kk < KQ; ++kk) bq[kk] = arrived(raw[kk]);
+    }
 
     f32x16 acc[DT];
 #pragma unroll
@@ -219,14 +248,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 
         f32x16 st[2];
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
+        for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) st[kt][v] = 0.f;
 #pragma unroll
-            for (int kk = 0; kk < KQ; ++kk)
-                st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<STRIDE>(tK, kt * 32, kk, lane), bq[kk],
-                                                                st[kt], 0, 0, 0);
+        for (int r = 0; r < DH / 64; ++r) {
+            bf16x8 ka[KQ / (DH / 64)][2];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt) ka[kk][kt] = frag_row<STRIDE>(tK, kt * 32, 4 * r + kk, lane);
+            sched_fence();
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+                    st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk][kt], bq[4 * r + kk], st[kt], 0, 0, 0);
         }
+        sched_fence();
+        bf16x8 va[2][2][DT];       // of the first 32 keys for wide heads, of all 64 for narrow ones
+        auto read_v = [&](int kt) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int t = 0; t < DT; ++t) va[DH == 64 ? kt : 0][ks][t] = frag_tr<STRIDE>(tV, kt * 32, ks, t * 32, lane);
+        };
+        read_v(0);
+        if constexpr (DH == 64) read_v(1);
+        sched_fence();
         // Softmax in the log2 domain on the raw scores: x = c*s, p = exp2(c*s - m).
         // Masks only where a block touches the diagonal or the padding edge
         // (wave-uniform test); everything else is one max, one fma, one exp2 and
@@ -270,15 +319,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
         l_run += lsum;
         // O^T += V^T P^T
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
+        for (int kt = 0; kt < 2; ++kt) {
+            if constexpr (DH != 64)
+                if (kt) { sched_fence(); read_v(1); sched_fence(); }
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
                 const bf16x8 pb = pack8(st[kt], 8 * ks);
 #pragma unroll
                 for (int t = 0; t < DT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<STRIDE>(tV, kt * 32, ks, t * 32, lane),
-                                                                     pb, acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[DH == 64 ? kt : 0][ks][t], pb, acc[t], 0, 0, 0);
             }
+        }
     }
 
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
@@ -317,11 +368,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
     const bool key_dead = key >= klimit;     // padding: this lane's key is visible to nobody
 
     bf16x8 bk[KQ], bv[KQ];      // B operands: n = key, k = head dimension
-#pragma unroll
-    for (int kk = 0; kk < KQ; ++kk) {
+    {
         const bf16* krow = base + D + (long)key * ld;
-        bk[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(krow, kk * 16 + 8 * half, dh, key < s));
-        bv[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(krow + D, kk * 16 + 8 * half, dh, key < s));
+        u32x4 rk[KQ], rv[KQ];
+#pragma unroll
+        for (int kk = 0; kk < KQ; ++kk) {
+            rk[kk] = load_head8<RAGGED>(krow, kk * 16 + 8 * half, dh, key < s);
+            rv[kk] = load_head8<RAGGED>(krow + D, kk * 16 + 8 * half, dh, key < s);
+        }
+#pragma unroll
+        for (int kk = 0; kk < KQ; ++kk) { bk[kk] = arrived(rk[kk]); bv[kk] = arrived(rv[kk]); }
     }
     f32x16 dk[4], dv[4];
 #pragma unroll
@@ -334,6 +390,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
     TileCopy<DH, BQ, 256, RAGGED> cQ, cdO;
     float stat_next = 0.f;      // threads 0..63: lse of query tid; 64..127: delta of query tid-64
     const float* stat_src = tid < BQ ? lse2 + (long)z * s + tid : delta + (long)z * s + (tid - BQ);
+    const float stat_mul = tid < BQ ? -1.0f / sl2 : -1.0f;
     // a query past the end gets probability 0 from an infinite log-sum-exp, and delta 0
     auto stat_at = [&](int q0) {
         if (RAGGED && q0 + tid % BQ >= s) return tid < BQ ? INFINITY : 0.f;
@@ -348,7 +405,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
         __syncthreads();
         cQ.store(tQ, tid);
         cdO.store(tdO, tid);
-        if (tid < 2 * BQ) sstat[tid / BQ][tid % BQ] = stat_next;
+        if (tid < 2 * BQ) sstat[tid / BQ][tid % BQ] = stat_next * stat_mul;
         __syncthreads();
         if (q0 + BQ < s) {
             cQ.fetch(base + (long)(q0 + BQ) * ld, ld, tid, s - q0 - BQ, dh);
@@ -359,33 +416,54 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
         if (CAUSAL && q0 + BQ - 1 < k_wave) continue;      // none of these queries sees this wave's keys
 #pragma unroll
         for (int qt = 0; qt < 2; ++qt) {
+            // The accumulators start at -lse / (scale log2 e) and -delta, so that one product each gives
+            // the exponent's argument and dP - delta.
             f32x16 sc, dp;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { sc[v] = 0.f; dp[v] = 0.f; }
+            for (int gq = 0; gq < 4; ++gq) {
+                const f32x4 l4 = *(const f32x4*)&sstat[0][qt * 32 + 8 * gq + 4 * half];
+                const f32x4 d4 = *(const f32x4*)&sstat[1][qt * 32 + 8 * gq + 4 * half];
 #pragma unroll
-            for (int kk = 0; kk < KQ; ++kk) {
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<STRIDE>(tQ, qt * 32, kk, lane), bk[kk], sc, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<STRIDE>(tdO, qt * 32, kk, lane), bv[kk], dp, 0, 0, 0);
+                for (int e = 0; e < 4; ++e) { sc[4 * gq + e] = l4[e]; dp[4 * gq + e] = d4[e]; }
             }
+#pragma unroll
+            for (int r = 0; r < DH / 64; ++r) {
+                bf16x8 aq[4], ado[4];
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) {
+                    aq[kk] = frag_row<STRIDE>(tQ, qt * 32, 4 * r + kk, lane);
+                    ado[kk] = frag_row<STRIDE>(tdO, qt * 32, 4 * r + kk, lane);
+                }
+                sched_fence();
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) {
+                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aq[kk], bk[4 * r + kk], sc, 0, 0, 0);
+                    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ado[kk], bv[4 * r + kk], dp, 0, 0, 0);
+                }
+            }
+            sched_fence();
+            bf16x8 tq[2][DT], tdo[2][DT];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int t = 0; t < DT; ++t) {
+                    tdo[ks][t] = frag_tr<STRIDE>(tdO, qt * 32, ks, t * 32, lane);
+                    tq[ks][t] = frag_tr<STRIDE>(tQ, qt * 32, ks, t * 32, lane);
+                }
+            sched_fence();
             // masks only where this wave's keys meet the diagonal or the padding edge
             // (wave-uniform test): elsewhere one fma, one exp2, one sub, one mul per score
             const bool edge = CAUSAL ? (q0 + qt * 32 < k_wave + 31) : (k_wave + 31 >= klimit);
             auto probabilities = [&](auto masked) {
 #pragma unroll
-                for (int gq = 0; gq < 4; ++gq) {
-                    const f32x4 l4 = *(const f32x4*)&sstat[0][qt * 32 + 8 * gq + 4 * half];
-                    const f32x4 d4 = *(const f32x4*)&sstat[1][qt * 32 + 8 * gq + 4 * half];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int v = 4 * gq + e;
-                        float p = exp2_raw(fmaf(sc[v], sl2, -l4[e]));
-                        if constexpr (decltype(masked)::value) {
-                            const int q = q0 + qt * 32 + 8 * gq + 4 * half + e;
-                            if ((CAUSAL && key > q) || key_dead) p = 0.f;
-                        }
-                        sc[v] = p;
-                        dp[v] = p * (dp[v] - d4[e]);     // the factor `scale` of dS is applied to dK at the end
+                for (int v = 0; v < 16; ++v) {
+                    float x = sc[v] * sl2;
+                    if constexpr (decltype(masked)::value) {
+                        const int q = q0 + qt * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+                        x = ((CAUSAL && key > q) || key_dead) ? -INFINITY : x;     // before the exponential: a select, no branch
                     }
+                    sc[v] = exp2_raw(x);
+                    dp[v] *= sc[v];          // the factor `scale` of dS is applied to dK at the end
                 }
             };
             if (edge) probabilities(std::true_type{}); else probabilities(std::false_type{});
@@ -394,8 +472,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 
                 const bf16x8 pb = pack8(sc, 8 * ks), dsb = pack8(dp, 8 * ks);
 #pragma unroll
                 for (int t = 0; t < DT; ++t) {
-                    dv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<STRIDE>(tdO, qt * 32, ks, t * 32, lane), pb, dv[t], 0, 0, 0);
-                    dk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<STRIDE>(tQ, qt * 32, ks, t * 32, lane), dsb, dk[t], 0, 0, 0);
+                    dv[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tdo[ks][t], pb, dv[t], 0, 0, 0);
+                    dk[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tq[ks][t], dsb, dk[t], 0, 0, 0);
                 }
             }
         }
@@ -434,20 +512,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     const bool q_ok = !RAGGED || q < s;
 
     bf16x8 bq[KQ], bdo[KQ];     // B operands: n = query, k = head dimension
-#pragma unroll
-    for (int kk = 0; kk < KQ; ++kk) {
-        bq[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(base + (long)q * ld, kk * 16 + 8 * half, dh, q_ok));
-        bdo[kk] = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(dO + ((long)b * s + q) * D + (long)h * dh, kk * 16 + 8 * half, dh, q_ok));
-    }
     float delta_q = 0.f;
+    {
+        const bf16* dorow = dO + ((long)b * s + q) * D + (long)h * dh;
+        const bf16* orow = O + ((long)b * s + q) * D + (long)h * dh;
+        u32x4 rq[KQ], rdo[KQ], ro[KQ];
 #pragma unroll
-    for (int kk = 0; kk < KQ; ++kk) {
-        const bf16x8 o = __builtin_bit_cast(bf16x8, load_head8<RAGGED>(O + ((long)b * s + q) * D + (long)h * dh, kk * 16 + 8 * half, dh, q_ok));
+        for (int kk = 0; kk < KQ; ++kk) {
+            rq[kk] = load_head8<RAGGED>(base + (long)q * ld, kk * 16 + 8 * half, dh, q_ok);
+            rdo[kk] = load_head8<RAGGED>(dorow, kk * 16 + 8 * half, dh, q_ok);
+            ro[kk] = load_head8<RAGGED>(orow, kk * 16 + 8 * half, dh, q_ok);
+        }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) delta_q += (float)bdo[kk][e] * (float)o[e];
+        for (int kk = 0; kk < KQ; ++kk) {
+            bq[kk] = arrived(rq[kk]);
+            bdo[kk] = arrived(rdo[kk]);
+            const bf16x8 o = arrived(ro[kk]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) delta_q += (float)bdo[kk][e] * (float)o[e];
+        }
     }
     delta_q += __shfl_xor(delta_q, 32, 64);
-    const float lse_q = q_ok ? lse2[(long)z * s + q] : 0.f;
+    // As in the dK / dV kernel the accumulators start at -lse / (scale log2 e) and -delta. Two sets of
+    // 16 registers hold these over the loop, which 128 columns do not leave free (70 spilled).
+    constexpr bool FOLD = DH == 64;
+    const float neg_lse = q_ok ? -lse2[(long)z * s + q] / (FOLD ? sl2 : 1.0f) : 0.f;
     if (half == 0 && q_ok) delta[(long)z * s + q] = delta_q;
     f32x16 dq[4];
 #pragma unroll
@@ -478,23 +567,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
         for (int kt = 0; kt < 2; ++kt) {
             f32x16 sc, dp;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { sc[v] = 0.f; dp[v] = 0.f; }
+            for (int v = 0; v < 16; ++v) { sc[v] = FOLD ? neg_lse : 0.f; dp[v] = FOLD ? -delta_q : 0.f; }
+            bf16x8 tk[2][DT];
+            auto read_tk = [&](int ks) {
 #pragma unroll
-            for (int kk = 0; kk < KQ; ++kk) {
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<STRIDE>(tK, kt * 32, kk, lane), bq[kk], sc, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<STRIDE>(tV, kt * 32, kk, lane), bdo[kk], dp, 0, 0, 0);
+                for (int t = 0; t < DT; ++t) tk[ks][t] = frag_tr<STRIDE>(tK, kt * 32, ks, t * 32, lane);
+            };
+            if constexpr (DH == 64) {
+                bf16x8 ak[KQ], av[KQ];
+#pragma unroll
+                for (int kk = 0; kk < KQ; ++kk) {
+                    ak[kk] = frag_row<STRIDE>(tK, kt * 32, kk, lane);
+                    av[kk] = frag_row<STRIDE>(tV, kt * 32, kk, lane);
+                }
+                sched_fence();
+#pragma unroll
+                for (int kk = 0; kk < KQ; ++kk) {
+                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak[kk], bq[kk], sc, 0, 0, 0);
+                    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[kk], bdo[kk], dp, 0, 0, 0);
+                }
+                sched_fence();
+                read_tk(0);
+                read_tk(1);
+                sched_fence();
+            } else {          // no registers left to read ahead (tried: 82 spilled, 95 -> 180 us at 32 heads of 128, 2048 tokens)
+#pragma unroll
+                for (int kk = 0; kk < KQ; ++kk) {
+                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<STRIDE>(tK, kt * 32, kk, lane), bq[kk], sc, 0, 0, 0);
+                    dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_row<STRIDE>(tV, kt * 32, kk, lane), bdo[kk], dp, 0, 0, 0);
+                }
             }
             // masks only where the key tile meets this wave's diagonal or the padding edge (wave-uniform)
             const bool edge = CAUSAL ? (k0 + kt * 32 + 31 > q_wave) : (k0 + kt * 32 + 31 >= klimit);
             auto dscores = [&](auto masked) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    float p = exp2_raw(fmaf(sc[v], sl2, -lse_q));
+                    float x = FOLD ? sc[v] * sl2 : fmaf(sc[v], sl2, neg_lse);
                     if constexpr (decltype(masked)::value) {
                         const int key = k0 + kt * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                        if ((CAUSAL && key > q) || (!CAUSAL && key >= klimit)) p = 0.f;   // causal stages carry no padding mask
+                        x = (CAUSAL ? key > q : key >= klimit) ? -INFINITY : x;   // causal stages carry no padding mask
                     }
-                    dp[v] = p * (dp[v] - delta_q);       // the factor `scale` of dS is applied to dQ at the end
+                    dp[v] = exp2_raw(x) * (FOLD ? dp[v] : dp[v] - delta_q);       // the factor `scale` of dS is applied to dQ at the end
                 }
             };
             // (at head dimension 128 the second copy of the loop body costs 14 spilled registers
@@ -502,10 +615,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
             if (DH == 128 || edge) dscores(std::true_type{}); else dscores(std::false_type{});
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) {
+                if constexpr (DH != 64) read_tk(ks);
                 const bf16x8 dsb = pack8(dp, 8 * ks);
 #pragma unroll
                 for (int t = 0; t < DT; ++t)
-                    dq[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr<STRIDE>(tK, kt * 32, ks, t * 32, lane), dsb, dq[t], 0, 0, 0);
+                    dq[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tk[ks][t], dsb, dq[t], 0, 0, 0);
             }
         }
     }
