@@ -517,51 +517,48 @@ int gemm(amdp_stage* st, GemmLayout lay, GemmArgs g, long lda, long ldb) {
 }
 
 // ---- typed launch helpers ---------------------------------------------------
-// 16-byte vectors per lane of the LayerNorm kernels that keep a row in registers
-// (1, 2, 4, 8 or 16: rows up to 64 * 16 vectors), 0 when the row is longer.
-template <class T>
-inline int ln_reg_vectors(int D) {
-    constexpr int V = Vec<T>::N;
-    if (D % V) return 0;
-    const int need = (D / V + 63) / 64;
-    for (int nv : {1, 2, 4, 8, 16})
-        if (need <= nv) return nv;
-    return 0;
-}
+// Calls KERN(NV, WPR) for the LayerNorm kernel that keeps a row of D in registers, or GENERIC for longer
+// rows. A wave to a row for up to two 16-byte vectors a lane (rows it could not divide by four waves
+// without idle lanes), a workgroup to a row for more. Wave -> workgroup in us (forward, backward): 2048
+// rows of 4096 13.2 -> 11.1, 19.2 -> 16.5; 1024 rows of 8192 17.7 -> 12.3, 26.3 -> 17.1; 512 rows of 2048
+// 7.3 -> 6.5, 8.4 -> 6.5; 4096 rows of 2048 11.2 -> 11.5, 15.0 -> 14.2; 4096 rows of 1600 10.5 -> 10.9,
+// 13.4 -> 12.5: MANY (the forward with at least LN_FWD_WAVE_ROWS rows) stays with waves for up to four.
+constexpr int LN_FWD_WAVE_ROWS = 4096;
+#define LN_ROW_KERNEL(T, D, MANY, KERN, GENERIC)                                                          \
+    do {                                                                                                  \
+        const int vectors_ = (D) % Vec<T>::N ? 1 << 30 : ((D) / Vec<T>::N + 63) / 64;                     \
+        if (vectors_ <= 1) KERN(1, 1);                                                                    \
+        else if (vectors_ <= 2) KERN(2, 1);                                                               \
+        else if (vectors_ <= 4 && (MANY)) KERN(4, 1);                                                     \
+        else if (vectors_ <= 4) KERN(1, 4);                                                               \
+        else if (vectors_ <= 8) KERN(2, 4);                                                               \
+        else if (vectors_ <= 16) KERN(4, 4);                                                              \
+        else GENERIC;                                                                                     \
+    } while (0)
+
 template <class T>
 int launch_ln_fwd(hipStream_t s, const void* x, const void* gamma, const void* beta, void* y, float* stats, int N,
                   int D, float eps) {
-    const dim3 grid((N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK);
-#define LN_FWD(KERN) hipLaunchKernelGGL(KERN, grid, dim3(256), 0, s, (const T*)x, (const T*)gamma, (const T*)beta, (T*)y, stats, N, D, eps)
-    switch (ln_reg_vectors<T>(D)) {
-        case 1: LN_FWD((ln_fwd_reg_kernel<T, 1>)); break;
-        case 2: LN_FWD((ln_fwd_reg_kernel<T, 2>)); break;
-        case 4: LN_FWD((ln_fwd_reg_kernel<T, 4>)); break;
-        case 8: LN_FWD((ln_fwd_reg_kernel<T, 8>)); break;
-        case 16: LN_FWD((ln_fwd_reg_kernel<T, 16>)); break;
-        default: LN_FWD(ln_fwd_kernel<T>);
-    }
+#define LN_ARGS dim3(256), 0, s, (const T*)x, (const T*)gamma, (const T*)beta, (T*)y, stats, N, D, eps
+#define LN_FWD(NV, WPR) hipLaunchKernelGGL((ln_fwd_reg_kernel<T, NV, WPR>), dim3(WPR == 1 ? (N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK : N), LN_ARGS)
+    LN_ROW_KERNEL(T, D, N >= LN_FWD_WAVE_ROWS, LN_FWD, hipLaunchKernelGGL(ln_fwd_kernel<T>, dim3((N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK), LN_ARGS));
 #undef LN_FWD
+#undef LN_ARGS
     return after_launch();
 }
 
 template <class T>
 int launch_ln_bwd(hipStream_t s, const void* dy, const void* x, const float* stats, const void* gamma,
                   const void* res, void* dx, int N, int D) {
-    const dim3 grid((N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK);
-#define LN_BWD(KERN) hipLaunchKernelGGL(KERN, grid, dim3(256), 0, s, (const T*)dy, (const T*)x, stats, (const T*)gamma, \
-                                        (const T*)res, (T*)dx, N, D)
-    switch (ln_reg_vectors<T>(D)) {
-        case 1: LN_BWD((ln_bwd_reg_kernel<T, 1>)); break;
-        case 2: LN_BWD((ln_bwd_reg_kernel<T, 2>)); break;
-        case 4: LN_BWD((ln_bwd_reg_kernel<T, 4>)); break;
-        case 8: LN_BWD((ln_bwd_reg_kernel<T, 8>)); break;
-        case 16: LN_BWD((ln_bwd_reg_kernel<T, 16>)); break;
-        default: LN_BWD(ln_bwd_kernel<T>);
-    }
+#define LN_ARGS dim3(256), 0, s, (const T*)dy, (const T*)x, stats, (const T*)gamma, (const T*)res, (T*)dx, N, D
+#define LN_BWD(NV, WPR) hipLaunchKernelGGL((ln_bwd_reg_kernel<T, NV, WPR>), dim3(WPR == 1 ? (N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK : N), LN_ARGS)
+    LN_ROW_KERNEL(T, D, false, LN_BWD, hipLaunchKernelGGL(ln_bwd_kernel<T>, dim3((N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK), LN_ARGS));
 #undef LN_BWD
+#undef LN_ARGS
     return after_launch();
 }
+#undef LN_ROW_KERNEL
+
 template <class T>
 int ln_fwd(amdp_stage* st, const void* x, const void* gamma, const void* beta, void* y, float* stats) {
     const Dims& d = st->d;
