@@ -464,6 +464,75 @@ __global__ __launch_bounds__(256) void colsum_batch_partial_kernel(ColSumBatch b
     }
 }
 
+// All of it in ONE launch, for few rows: a workgroup owns CS_COLS 16-byte vectors of columns and
+// every row, 32 rows side by side and four of each lane's in flight; the 32 sums of a column are
+// added in order through LDS. Segments are numbered in these narrower blocks (first_block).
+// Bound by the chain of N / 128 loads; two launches have shorter chains, but cost two starts
+// (333 x 1000 fp32 through the entry points, all row operators: 39.1 -> 33.2 us).
+constexpr int CS_COLS = 8, CS_ROWS = 256 / CS_COLS;
+template <class T>
+__global__ __launch_bounds__(256) void colsum_rows_kernel(ColSumBatch b, int accumulate) {
+    constexpr int V = Vec<T>::N;
+    typedef typename RawVec<T>::type raw_t;
+    __shared__ float red[2][CS_ROWS][CS_COLS * V];
+    int si = 0;
+    for (int i = 1; i < b.n; ++i)
+        if ((int)blockIdx.x >= b.seg[i].first_block) si = i;
+    const T* dy = (const T*)b.seg[si].dy;
+    const T* x = (const T*)b.seg[si].x;
+    const float* stats = b.seg[si].stats;
+    const int C = b.seg[si].C;
+    const bool ln = x != nullptr;                   // uniform over the block
+    const int cl = threadIdx.x % CS_COLS, rg = threadIdx.x / CS_COLS;
+    const int c_blk = (blockIdx.x - b.seg[si].first_block) * CS_COLS * V, c0 = c_blk + cl * V;
+    float s[V], sg[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) { s[i] = 0.f; sg[i] = 0.f; }
+    if (c0 < C) {
+        for (int r = rg; r < b.N; r += 4 * CS_ROWS) {
+            raw_t dv[4], xv[4];
+            float mean[4], rstd[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int ru = r + u * CS_ROWS;
+                if (ru < b.N) {
+                    dv[u] = *(const raw_t*)(dy + (long)ru * C + c0);
+                    if (ln) {
+                        xv[u] = *(const raw_t*)(x + (long)ru * C + c0);
+                        mean[u] = stats[2 * ru];
+                        rstd[u] = stats[2 * ru + 1];
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (r + u * CS_ROWS < b.N)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) {
+                        const float dd = (float)dv[u][i];
+                        if (ln) sg[i] += dd * ((float)xv[u][i] - mean[u]) * rstd[u];
+                        s[i] += dd;
+                    }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        red[0][rg][cl * V + i] = ln ? sg[i] : s[i];
+        red[1][rg][cl * V + i] = s[i];
+    }
+    __syncthreads();
+    // out: the plain sums, or the gain's and behind them the bias's
+    for (int j = threadIdx.x; j < (ln ? 2 : 1) * CS_COLS * V; j += 256) {
+        const int part = j / (CS_COLS * V), jc = j % (CS_COLS * V);
+        if (c_blk + jc >= C) continue;
+        float t = 0.f;
+#pragma unroll
+        for (int g = 0; g < CS_ROWS; ++g) t += red[part][g][jc];
+        float* o = b.seg[si].out + (long)part * C + c_blk + jc;
+        *o = accumulate ? *o + t : t;
+    }
+}
+
 // Second stage over the concatenated width: column j belongs to the segment whose
 // [woff, woff + width) holds it and goes to that segment's output vector.
 __global__ __launch_bounds__(256) void colsum_batch_final_kernel(ColSumBatch b, const float* __restrict__ partial,

@@ -566,6 +566,23 @@ int ln_fwd(amdp_stage* st, const void* x, const void* gamma, const void* beta, v
     return launch_ln_fwd<T>(st->launch, x, gamma, beta, y, stats, d.N, d.D, st->cfg.ln_eps);
 }
 
+// Up to this many rows one launch does all column sums of a batch (colsum_rows_kernel); beyond, its chain
+// of loads is longer than a second launch. A layer's sums, one launch / two in us at 64, 256, 384, 512 and
+// 1024 rows: 192 wide bf16 6.7 / 10.6, 9.0 / 10.1, 10.6 / 10.4, 12.1 / 10.5, 19.9 / 10.6; 4096 wide bf16
+// 7.5 / 12.2, 15.0 / 18.7, 18.7 / 22.5, 23.6 / 26.2, 35.7 / 33.8; 512 wide fp32 6.2 / 9.9, 8.7 / 10.3,
+// 9.8 / 10.6, 11.3 / 11.1, 18.1 / 13.5.
+constexpr int COLSUM_ONE_LAUNCH_ROWS = 384;
+template <class T>
+int launch_colsum_rows(hipStream_t s, ColSumBatch b, int accumulate) {
+    int blocks = 0;
+    for (int i = 0; i < b.n; ++i) {
+        b.seg[i].first_block = blocks;
+        blocks += (b.seg[i].C + CS_COLS * Vec<T>::N - 1) / (CS_COLS * Vec<T>::N);
+    }
+    hipLaunchKernelGGL(colsum_rows_kernel<T>, dim3(blocks), dim3(256), 0, s, b, accumulate);
+    return after_launch();
+}
+
 // Column sums in two deterministic stages through `partial` (fp32 [chunks][width]).
 // The split of the rows: enough chunks to put ~8 blocks on every compute unit, at
 // least 16 rows each (a wave then has four rows' loads in flight), at most
@@ -583,11 +600,16 @@ inline ColSumPlan plan_column_sums(int N, int C, int vec, int n_cu, int max_chun
 template <class T, bool LN>
 int launch_column_sums(hipStream_t s, const void* dy, const void* x, const float* stats, float* partial, float* out,
                        int N, int C, const ColSumPlan& p, int accumulate) {
-    if (p.chunks > 0) {      // no rows: the second stage alone writes zeros
-        hipLaunchKernelGGL((colreduce_partial_kernel<T, LN>), dim3(p.col_blocks, p.chunks), dim3(256), 0, s,
-                           (const T*)dy, (const T*)x, stats, partial, N, C, p.rows_per_chunk);
-        TRY(after_launch());
+    if (N <= COLSUM_ONE_LAUNCH_ROWS) {
+        ColSumBatch b{};
+        b.n = 1;
+        b.N = N;
+        b.seg[0].dy = dy; b.seg[0].x = LN ? x : nullptr; b.seg[0].stats = stats; b.seg[0].out = out; b.seg[0].C = C;
+        return launch_colsum_rows<T>(s, b, accumulate);
     }
+    hipLaunchKernelGGL((colreduce_partial_kernel<T, LN>), dim3(p.col_blocks, p.chunks), dim3(256), 0, s,
+                       (const T*)dy, (const T*)x, stats, partial, N, C, p.rows_per_chunk);
+    TRY(after_launch());
     const int width = LN ? 2 * C : C;
     hipLaunchKernelGGL(colreduce_final_kernel, dim3((width + 15) / 16), dim3(256), 0, s, partial, out, width,
                        p.chunks, accumulate);
@@ -615,6 +637,10 @@ void colsum_add(ColSumList& L, const void* dy, const void* x, const float* stats
 template <class T>
 int colsum_flush(amdp_stage* st, ColSumList& L) {
     if (L.b.n == 0) return AMDP_OK;
+    if (L.b.N <= COLSUM_ONE_LAUNCH_ROWS) {
+        ProfScope ps(st, "column_sums", 0.0, L.bytes);
+        return launch_colsum_rows<T>(st->launch, L.b, st->fused_acc ? 1 : 0);
+    }
     // ~8 blocks per compute unit, at least 16 rows per chunk (four rows' loads in flight per wave)
     int chunks = std::min(st->w.partial_chunks, std::max(1, 8 * st->n_cu / L.blocks));
     L.b.rows_per_chunk = std::max(16, (L.b.N + chunks - 1) / chunks);

@@ -1,5 +1,6 @@
 """LayerNorm forward and backward around the row lengths at which a workgroup takes over a row from a wave, and around
-the number of rows that decides it for the forward, against float64 on the CPU."""
+the number of rows that decides it for the forward; column sums around the number of rows up to which one launch does
+them. Against float64 on the CPU."""
 import pytest
 import torch
 
@@ -34,3 +35,30 @@ def test_rows(rows, vectors, dtype, residual):
         scale = tol if got.dtype == dt else 2e-6
         err = (got.cpu().double() - want).abs().max().item()
         assert err <= scale * max(1.0, want.abs().max().item()), (err, want.abs().max().item())
+
+
+@pytest.mark.parametrize("layernorm", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("rows,vectors", [(1, 1), (31, 7), (32, 8), (33, 9), (127, 250), (129, 64), (384, 17), (385, 17)])
+def test_column_sums(rows, vectors, dtype, layernorm):
+    dt, n = (torch.bfloat16, 8) if dtype == "bf16" else (torch.float32, 4)
+    cols = vectors * n
+    g = torch.Generator().manual_seed(rows * 4099 + cols)
+    dy, x = (torch.randn((rows, cols), generator=g).to(dt) for _ in range(2))
+    stats = torch.stack([0.1 * torch.randn(rows, generator=g), 1 + 0.1 * torch.rand(rows, generator=g)], 1).contiguous()
+    out = torch.full(((2 if layernorm else 1) * cols,), 7.0, dtype=torch.float32, device="cuda:0")
+    ws = torch.empty(amdp.amdp_column_sums_workspace_bytes(rows, cols, amdp.BF16 if dtype == "bf16" else amdp.FP32, layernorm),
+                     dtype=torch.uint8, device="cuda:0")
+    amdp.amdp_column_sums(dy.cuda(), x.cuda() if layernorm else None, stats.cuda() if layernorm else None, out, ws)
+    dy, x, stats = dy.double(), x.double(), stats.double()
+    parts = ([dy * (x - stats[:, :1]) * stats[:, 1:]] if layernorm else []) + [dy]
+    want, size = (torch.cat([f(p).sum(0) for p in parts]) for f in (lambda p: p, torch.abs))
+    # an fp32 sum of `rows` terms: fewer than 32 roundings in a row in any order used, each 2^-24 of the sum of magnitudes
+    assert torch.all((out.cpu().double() - want).abs() <= 32 * 2.0 ** -24 * size + 1e-30)
+
+
+def test_column_sums_of_no_rows():
+    out = torch.full((24,), 7.0, dtype=torch.float32, device="cuda:0")
+    ws = torch.empty(amdp.amdp_column_sums_workspace_bytes(0, 24, amdp.BF16, False), dtype=torch.uint8, device="cuda:0")
+    amdp.amdp_column_sums(torch.empty((0, 24), dtype=torch.bfloat16, device="cuda:0"), None, None, out, ws)
+    assert torch.all(out == 0)
