@@ -16,7 +16,7 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const T* __restrict__ E,
                                                        int N, int s, int D, int V) {
     constexpr int VEC = Vec<T>::N;
     const int lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const long row = row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     if (row >= N) return;
     const T* e = E + (long)clamp_token(tokens[row], V) * D;
     const T* p = P + (row % s) * D;

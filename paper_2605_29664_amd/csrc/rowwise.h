@@ -41,6 +41,16 @@ __device__ __forceinline__ void store_vec(T* p, const float (&in)[Vec<T>::N]) {
 
 constexpr int ROWS_PER_BLOCK = 4;   // 256 threads
 
+// Workgroup number of a kernel launched with row_grid: a dimension of a grid holds fewer than
+// 2^32 lanes (a larger one wraps without an error), so from ROW_GRID_X workgroups on the rest of
+// them is counted by the grid's second dimension.
+constexpr int ROW_GRID_X = 1 << 20;
+__device__ __forceinline__ long row_block() { return (long)blockIdx.y * ROW_GRID_X + blockIdx.x; }
+inline long row_blocks(long rows) { return (rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK; }     // a wave to a row
+inline dim3 row_grid(long blocks) {
+    return blocks <= ROW_GRID_X ? dim3((unsigned)blocks) : dim3(ROW_GRID_X, (unsigned)((blocks + ROW_GRID_X - 1) / ROW_GRID_X));
+}
+
 // ------------------------------------------------------------------ LayerNorm
 // y = (x - mean) * rstd * gamma + beta, biased variance; stats[2r] = mean, stats[2r+1] = rstd.
 template <class T>
@@ -49,7 +59,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, co
                                                      float* __restrict__ stats, int N, int D, float eps) {
     constexpr int V = Vec<T>::N;
     const int lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const long row = row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     if (row >= N) return;
     const T* xr = x + row * D;
     const int nv = D / V;
@@ -90,7 +100,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T* __restrict__ dy, c
                                                      T* dx, int N, int D) {
     constexpr int V = Vec<T>::N;
     const int lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const long row = row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     if (row >= N) return;
     const float mean = stats[2 * row], rstd = stats[2 * row + 1];
     const T* xr = x + row * D;
@@ -177,7 +187,7 @@ __global__ __launch_bounds__(256) void ln_fwd_reg_kernel(const T* __restrict__ x
     typedef typename RawVec<T>::type raw_t;
     __shared__ float red[2][WPR];
     const int lane = WPR == 1 ? threadIdx.x & 63 : threadIdx.x;
-    const long row = WPR == 1 ? (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6) : (long)blockIdx.x;
+    const long row = WPR == 1 ? row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6) : row_block();
     if (row >= N) return;
     const int nv = D / V;
     const raw_t* xr = (const raw_t*)(x + row * D);
@@ -236,7 +246,7 @@ __global__ __launch_bounds__(256) void ln_bwd_reg_kernel(const T* __restrict__ d
     typedef typename RawVec<T>::type raw_t;
     __shared__ float red[WPR][2];
     const int lane = WPR == 1 ? threadIdx.x & 63 : threadIdx.x;
-    const long row = WPR == 1 ? (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6) : (long)blockIdx.x;
+    const long row = WPR == 1 ? row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6) : row_block();
     if (row >= N) return;
     const int nv = D / V;
     const raw_t* xr = (const raw_t*)(x + row * D);
@@ -608,7 +618,7 @@ __global__ __launch_bounds__(256) void softmax_fwd_kernel(T* S, long rows, int s
                                                           const int32_t* __restrict__ valid_len, int H) {
     constexpr int V = Vec<T>::N;
     const int lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const long row = row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     if (row >= rows) return;
     const int q = (int)(row % s);
     const long z = row / s;
@@ -650,7 +660,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_kernel(const T* __restrict__ 
                                                           const int32_t* __restrict__ valid_len, int H) {
     constexpr int V = Vec<T>::N;
     const int lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const long row = row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     if (row >= rows) return;
     const int q = (int)(row % s);
     const long z = row / s;
@@ -686,7 +696,7 @@ __global__ __launch_bounds__(256) void ce_fwd_kernel(T* logits, const int32_t* _
                                                      float* __restrict__ row_loss, int N, int Vocab, long ld) {
     constexpr int V = Vec<T>::N;
     const int lane = threadIdx.x & 63;
-    const long row = (long)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const long row = row_block() * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     if (row >= N) return;
     T* p = logits + row * ld;
     const int nv = (int)(ld / V);

@@ -540,8 +540,8 @@ template <class T>
 int launch_ln_fwd(hipStream_t s, const void* x, const void* gamma, const void* beta, void* y, float* stats, int N,
                   int D, float eps) {
 #define LN_ARGS dim3(256), 0, s, (const T*)x, (const T*)gamma, (const T*)beta, (T*)y, stats, N, D, eps
-#define LN_FWD(NV, WPR) hipLaunchKernelGGL((ln_fwd_reg_kernel<T, NV, WPR>), dim3(WPR == 1 ? (N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK : N), LN_ARGS)
-    LN_ROW_KERNEL(T, D, N >= LN_FWD_WAVE_ROWS, LN_FWD, hipLaunchKernelGGL(ln_fwd_kernel<T>, dim3((N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK), LN_ARGS));
+#define LN_FWD(NV, WPR) hipLaunchKernelGGL((ln_fwd_reg_kernel<T, NV, WPR>), row_grid(WPR == 1 ? row_blocks(N) : N), LN_ARGS)
+    LN_ROW_KERNEL(T, D, N >= LN_FWD_WAVE_ROWS, LN_FWD, hipLaunchKernelGGL(ln_fwd_kernel<T>, row_grid(row_blocks(N)), LN_ARGS));
 #undef LN_FWD
 #undef LN_ARGS
     return after_launch();
@@ -551,8 +551,8 @@ template <class T>
 int launch_ln_bwd(hipStream_t s, const void* dy, const void* x, const float* stats, const void* gamma,
                   const void* res, void* dx, int N, int D) {
 #define LN_ARGS dim3(256), 0, s, (const T*)dy, (const T*)x, stats, (const T*)gamma, (const T*)res, (T*)dx, N, D
-#define LN_BWD(NV, WPR) hipLaunchKernelGGL((ln_bwd_reg_kernel<T, NV, WPR>), dim3(WPR == 1 ? (N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK : N), LN_ARGS)
-    LN_ROW_KERNEL(T, D, false, LN_BWD, hipLaunchKernelGGL(ln_bwd_kernel<T>, dim3((N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK), LN_ARGS));
+#define LN_BWD(NV, WPR) hipLaunchKernelGGL((ln_bwd_reg_kernel<T, NV, WPR>), row_grid(WPR == 1 ? row_blocks(N) : N), LN_ARGS)
+    LN_ROW_KERNEL(T, D, false, LN_BWD, hipLaunchKernelGGL(ln_bwd_kernel<T>, row_grid(row_blocks(N)), LN_ARGS));
 #undef LN_BWD
 #undef LN_ARGS
     return after_launch();
@@ -745,7 +745,7 @@ int attention_fwd(amdp_stage* st, const void* qkv_, void* P_, void* o_, const in
     const long rows = (long)d.b * d.H * d.s;
     {
     ProfScope ps(st, "softmax_fwd", 0.0, (double)rows * d.s * sizeof(T) * (d.causal ? 1.5 : 2.0));
-    hipLaunchKernelGGL(softmax_fwd_kernel<T>, dim3((unsigned)((rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK)),
+    hipLaunchKernelGGL(softmax_fwd_kernel<T>, row_grid(row_blocks(rows)),
                        dim3(256), 0, st->launch, (T*)P_, rows, d.s, 1.0f / sqrtf((float)d.dh),
                        d.causal ? 1 : 0, valid, d.H);
     }
@@ -795,7 +795,7 @@ int attention_bwd(amdp_stage* st, const void* dO_, const void* qkv_, const void*
     const long rows = (long)d.b * d.H * d.s;
     {
     ProfScope ps(st, "softmax_bwd", 0.0, (double)rows * d.s * sizeof(T) * (d.causal ? 2.0 : 3.0));
-    hipLaunchKernelGGL(softmax_bwd_kernel<T>, dim3((unsigned)((rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK)),
+    hipLaunchKernelGGL(softmax_bwd_kernel<T>, row_grid(row_blocks(rows)),
                        dim3(256), 0, st->launch, (const T*)P_, (T*)dP_, rows, d.s, 1.0f / sqrtf((float)d.dh),
                        d.causal ? 1 : 0, valid, d.H);
     }
@@ -857,7 +857,7 @@ int forward_impl(amdp_stage* st, int aslot, int vslot, const void* X, const int3
     if (d.emb) {
         TRY(device_copy(st->launch, S + st->w.slot.tokens, aux, (size_t)d.N * 4));
         ProfScope ps(st, "embedding_fwd", 0.0, 3.0 * (double)ND);
-        hipLaunchKernelGGL(embed_fwd_kernel<T>, dim3((d.N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK), dim3(256), 0,
+        hipLaunchKernelGGL(embed_fwd_kernel<T>, row_grid(row_blocks(d.N)), dim3(256), 0,
                            st->launch, W + d.off_tok(), W + d.off_pos(), aux, (T*)(S + st->w.slot.layers[0].xin),
                            d.N, d.s, d.D, d.V);
         TRY(after_launch());
@@ -899,7 +899,7 @@ int forward_impl(amdp_stage* st, int aslot, int vslot, const void* X, const int3
         TRY(gemm(st, G_NT, g, d.D, d.D));
         float* row_loss = st->at<float>(st->w.row_loss);
         ProfScope ps(st, "cross_entropy", 0.0, (double)d.N * d.V * sizeof(T) * 2);
-        hipLaunchKernelGGL(ce_fwd_kernel<T>, dim3((d.N + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK), dim3(256), 0,
+        hipLaunchKernelGGL(ce_fwd_kernel<T>, row_grid(row_blocks(d.N)), dim3(256), 0,
                            st->launch, (T*)(S + sl.dlogits), aux, row_loss, d.N, d.V, d.Vld);
         TRY(after_launch());
         hipLaunchKernelGGL(mean_kernel, dim3(1), dim3(256), 0, st->launch, row_loss, (float*)out, d.N);
