@@ -317,13 +317,20 @@ inline bool hip_ok(hipError_t e, const char* what) {
 
 inline int after_launch() { return hip_ok(hipGetLastError(), "kernel launch") ? AMDP_OK : AMDP_E_HIP; }
 
+// 16-byte vectors (one to a lane) of one launch of the copy and the clear: a dimension of a grid
+// holds fewer than 2^32 lanes, and a larger one wraps without an error
+constexpr long FLAT_MAX_LANES = 1L << 31;
+
 // bytes is a multiple of 4; 16-byte path when both pointers allow it
 int device_copy(hipStream_t stream, void* dst, const void* src, size_t bytes) {
     if (!bytes) return AMDP_OK;
     if ((((uintptr_t)dst | (uintptr_t)src) & 15) == 0 && bytes % 16 == 0) {
         const long n16 = (long)(bytes / 16);
-        hipLaunchKernelGGL(copy16_kernel, dim3(direct_grid(n16, ACC_BLOCK)), dim3(ACC_BLOCK), 0, stream, (u32x4*)dst,
-                           (const u32x4*)src, n16);
+        for (long i = 0; i < n16; i += FLAT_MAX_LANES) {
+            const long n = std::min(n16 - i, FLAT_MAX_LANES);
+            hipLaunchKernelGGL(copy16_kernel, dim3(direct_grid(n, ACC_BLOCK)), dim3(ACC_BLOCK), 0, stream, (u32x4*)dst + i,
+                               (const u32x4*)src + i, n);
+        }
     } else {
         if ((((uintptr_t)dst | (uintptr_t)src) & 3) || bytes % 4) return AMDP_E_INVAL;
         const long n = (long)(bytes / 4);
@@ -336,7 +343,10 @@ int device_copy(hipStream_t stream, void* dst, const void* src, size_t bytes) {
 int device_zero(hipStream_t stream, void* dst, size_t bytes) {
     if (!bytes) return AMDP_OK;
     const long n16 = (long)(bytes / 16);
-    hipLaunchKernelGGL(zero16_kernel, dim3(direct_grid(n16, ACC_BLOCK)), dim3(ACC_BLOCK), 0, stream, (u32x4*)dst, n16);
+    for (long i = 0; i < n16; i += FLAT_MAX_LANES) {
+        const long n = std::min(n16 - i, FLAT_MAX_LANES);
+        hipLaunchKernelGGL(zero16_kernel, dim3(direct_grid(n, ACC_BLOCK)), dim3(ACC_BLOCK), 0, stream, (u32x4*)dst + i, n);
+    }
     return after_launch();
 }
 

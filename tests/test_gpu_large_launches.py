@@ -49,3 +49,19 @@ def test_layernorm_of_more_rows_than_2_to_24(vectors, forward):
         assert bool((out[first:min(first + 2**20, rows - 4)] == rest).all()), first
     del x, out, stats
     torch.cuda.empty_cache()
+
+
+def test_copy_of_more_than_64_gib():
+    """One 16-byte vector to a lane: 2^32 lanes move 64 GiB."""
+    _need(135)
+    n = 2**33 + 2**20                     # 64-bit words: 64 GiB and 8 MiB
+    src = torch.empty(n, dtype=torch.int64, device="cuda:0")
+    dst = torch.zeros(n, dtype=torch.int64, device="cuda:0")
+    parts = [slice(first, min(first + 2**28, n)) for first in range(0, n, 2**28)]
+    for p in parts:
+        src[p] = torch.arange(p.start + 1, p.stop + 1, device="cuda:0")
+    amdp.amdp_device_copy(dst, src)
+    for p in parts:
+        assert torch.equal(dst[p], torch.arange(p.start + 1, p.stop + 1, device="cuda:0")), p
+    del src, dst
+    torch.cuda.empty_cache()
