@@ -5,7 +5,8 @@
 // epilogue as gemm_mfma_kernel; no batch, no causal band, but any M, N and K that
 // are multiples of 8 (the row kernels' vector width, so every shape a bf16 stage
 // can have): the loads go through buffer descriptors that end where the operand
-// ends, and a lane past the end writes zeros into the tile.
+// ends, and a lane past the end writes zeros into the tile. An operand whose k rows
+// lie apart may be of any length: its descriptor starts at the k-tile being loaded.
 //
 // One such load moves 64 lanes x 16 bytes = 1 KB to consecutive LDS addresses
 // (lane l's 16 bytes land at base + 16 l), so a tile row cannot be padded.
@@ -95,13 +96,31 @@ struct DlTile {
             return (unsigned)krow * ld * 2 + ((((pb >> 6) ^ block_swizzle(krow)) << 6) | (pb & 63));
         }
     }
-    // Bytes of the operand from the tile's first element to the end of what the tile
-    // may read: `rows` m/n rows and K k exist from there on.
-    __device__ static __forceinline__ unsigned extent(int rows, int K, unsigned ld) {
-        if constexpr (!KM) return ((unsigned)(min(rows, R) - 1) * ld + (unsigned)K) * 2;
-        else return ((unsigned)(K - 1) * ld + (unsigned)rows) * 2;
+    // Bytes from the descriptor's start to the end of what may be read through it:
+    // `rows` m/n rows and `ks` k exist from there on. A k-contiguous operand keeps its
+    // descriptor and moves the scalar offset by 128 bytes a k-tile; an m/n-contiguous
+    // one, whose k rows would take that offset past 2 GiB (65536 tokens of a 16384-wide
+    // FFN), moves the descriptor itself and covers one k-tile.
+    __device__ static __forceinline__ unsigned extent(int rows, int ks, unsigned ld) {
+        if constexpr (!KM) return ((unsigned)(min(rows, R) - 1) * ld + (unsigned)ks) * 2;
+        else return ((unsigned)(min(ks, MF_BK) - 1) * ld + (unsigned)rows) * 2;
     }
-    __device__ static __forceinline__ unsigned ktile_gstride(unsigned ld) { return KM ? MF_BK * ld * 2 : MF_BK * 2; }
+    // The descriptor and scalar offset of the k-tile that starts at k; `last`: first k of the last
+    // tile; `whole`, `tail`: extents of a whole k-tile and of the last one. Past that the descriptor
+    // is empty and the offset 0 (zeros, no memory traffic). Scalar selects, no branch.
+    __device__ static __forceinline__ void advance(u32x4& rsrc, unsigned& soff, int k, int last, unsigned ld, unsigned whole,
+                                                   unsigned tail) {
+        if constexpr (!KM) {
+            soff = k <= last ? soff + MF_BK * 2 : 0;
+            if (k > last) rsrc[2] = 0;
+        } else {
+            const uint64_t a = ((uint64_t)rsrc[1] << 32 | rsrc[0]) + (uint64_t)MF_BK * 2 * ld;
+            rsrc[0] = (uint32_t)a;
+            rsrc[1] = (uint32_t)(a >> 32);
+            const unsigned e = k == last ? tail : whole;
+            rsrc[2] = k <= last ? e : 0;
+        }
+    }
 
     // Fragment addressing. `origin` = first row of the wave's part of the tile.
     // !KM: index = k-step (4 lane offsets), sub-tile j is an immediate.
@@ -298,8 +317,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_dl_kernel(GemmArgs g
 #pragma unroll
     for (int p = 0; p < TB::PW; ++p) vb_off[p] = TB::lane_goff(wave, lane, p, ldb, kb);
     unsigned sa_off = 0, sb_off = 0;
-    const unsigned a_step = TA::ktile_gstride(lda), b_step = TB::ktile_gstride(ldb);
-    const int nk = (K + MF_BK - 1) / MF_BK;
+    const int nk = (K + MF_BK - 1) / MF_BK, k_last = (nk - 1) * MF_BK;
+    const unsigned a_whole = TA::extent(g.M - m0, MF_BK, lda), a_tail = TA::extent(g.M - m0, K - k_last, lda);
+    const unsigned b_whole = TB::extent(g.N - n0, MF_BK, ldb), b_tail = TB::extent(g.N - n0, K - k_last, ldb);
     constexpr int NVM = TA::PW + TB::PW;
     constexpr int A_BYTES = RA * TA::BYTES;
     int ka_issue = 0, kb_issue = 0;            // first k of the operand tile being issued
@@ -312,20 +332,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_dl_kernel(GemmArgs g
         const unsigned v = (!B_KM && kb_issue + kb >= K) ? BUF_OOB : vb_off[p];
         load16_to_lds(rb, v, sb_off, lds + b_slot + (wave + NW * p) * 1024);
     };
-    // tiles past the last are issued with an empty descriptor and offset 0 (zeros, no memory
-    // traffic): the loop body has no branches and the count of loads in flight is fixed
+    // tiles past the last are issued too: the loop body has no branches and the count of
+    // loads in flight is fixed
     auto next_a = [&]() {
         ka_issue += MF_BK;
-        const bool more = ka_issue < K;
-        sa_off = more ? sa_off + a_step : 0;
-        if (!more) ra[2] = 0;
+        TA::advance(ra, sa_off, ka_issue, k_last, lda, a_whole, a_tail);
         a_slot = a_slot + TA::BYTES == A_BYTES ? 0 : a_slot + TA::BYTES;
     };
     auto next_b = [&]() {
         kb_issue += MF_BK;
-        const bool more = kb_issue < K;
-        sb_off = more ? sb_off + b_step : 0;
-        if (!more) rb[2] = 0;
+        TB::advance(rb, sb_off, kb_issue, k_last, ldb, b_whole, b_tail);
         b_slot = b_slot + TB::BYTES == A_BYTES + RB * TB::BYTES ? A_BYTES : b_slot + TB::BYTES;
     };
 
@@ -450,15 +466,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_dl_kernel(GemmArgs g
 }
 
 // True when the problem satisfies every assumption of gemm_mfma_dl_kernel (any tile):
-// whole 16-byte vectors along every row, and every descriptor below 2 GiB.
+// whole 16-byte vectors along every row, and every descriptor below 2 GiB (rows below 8 MiB).
 inline bool mfma_dl_shape_ok(const GemmArgs& g, bool a_km, bool b_km) {
     GemmArgs t = g;
     if (g.M % 8 || g.N % 8 || g.K % 8 || g.M <= 0 || g.N <= 0 || g.K <= 0 || g.batch != 1 || g.causal) return false;
     t.M = t.N = 64; t.K = MF_BK;
     if (!mfma_shape_ok<64, 64>(t, a_km, b_km)) return false;
     const long lda = a_km ? g.a_cs : g.a_rs, ldb = b_km ? g.b_rs : g.b_cs;
-    const long ea = a_km ? g.K * lda + g.M : 256 * lda + g.K, eb = b_km ? g.K * ldb + g.N : 256 * ldb + g.K;
-    constexpr long LIM = (1L << 30) - 4096 * 64;      // elements: 2 GiB less one k-tile's overshoot of the scalar offset
+    // elements that one descriptor covers: a k-tile of an m/n-contiguous operand, a tile's rows of a k-contiguous one
+    const long ea = a_km ? MF_BK * lda : 256 * lda + g.K, eb = b_km ? MF_BK * ldb : 256 * ldb + g.K;
+    constexpr long LIM = (1L << 30) - 4096 * 64;      // 2 GiB less the scalar offset's overshoot
     return ea < LIM && eb < LIM && lda < (1 << 22) && ldb < (1 << 22);
 }
 
