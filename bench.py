@@ -203,7 +203,7 @@ def main():
         result["side_stream"] = stage.amdp_stage_get_overlap()
         result["roofline"]["note"] = (("as timed: kernels of the side stream run concurrently, so a launch shares "
                                        "the compute units with others; see roofline_isolated") if result["side_stream"]
-                                      else "as timed: the side stream is off at this width, every kernel has the GPU to itself")
+                                      else "as timed: the side stream is off at this size, every kernel has the GPU to itself")
         def streaming(pr):
             out = {}
             for nm in ("grad_accumulate", "adam_update"):

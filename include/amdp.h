@@ -355,13 +355,13 @@ int amdp_apply_update(amdp_stage_t* stage, const amdp_adam_t* hp, uint32_t* new_
  * its activation slot.
  * on = 0 keeps everything on the caller's stream (used to time kernels in
  * isolation). Default: on while (d_model / 256)^2 is below the number of compute
- * units, off beyond (every product of the backward then fills the GPU on its
- * own and concurrency measured no gain). A stage whose leaves are shorter than the
- * hand-over to the side stream keeps them on the caller's stream also while this is on
- * by default; a call with on = 1, or AMDP_OPT_LEAF_FORKS, makes it use the side stream.
- * Results are bit-identical either way. */
+ * units and a layer's weight gradients (the vocabulary projection's share included)
+ * are more than 6e9 multiply-adds per minibatch, 1e9 in fp32; off beyond (every product
+ * of the backward then fills the GPU on its own and concurrency measured no gain) and
+ * below (the leaves are then shorter than the hand-over to the side stream). Results
+ * are bit-identical either way. */
 int amdp_stage_set_overlap(amdp_stage_t* stage, int32_t on);
-/* *on (host) <- 1 when the stage may use its side stream, else 0. */
+/* *on (host) <- 1 when the side stream is in use, else 0. */
 int amdp_stage_get_overlap(const amdp_stage_t* stage, int32_t* on);
 
 /* Copies the published weights of resident version `version` (Section 3.1: the

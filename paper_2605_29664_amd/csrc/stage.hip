@@ -268,9 +268,7 @@ struct amdp_stage {
     int last_leaves = -1;
     uint64_t free_seq[MAX_ASLOTS] = {};
     uint64_t free_counter = 0;
-    bool overlap = true;
-    bool leaf_inline = false;      // a small stage's leaves stay on the caller's stream (set at creation)
-    bool forks() const { return overlap && !leaf_inline; }
+    bool overlap = true;           // leaves go to the side stream (default set at creation)
     int leaf_forks = 0;            // side-stream forks per layer of a backward: 0 = one per leaf, 1, 2 (set at creation)
     bool fused_acc = false;        // backward adds parameter gradients into G directly
     // 0: the plan decides where contractions are split (gemm_plan.h); set by AMDP_OPT_SPLIT_K_MIN_TOKENS /
@@ -926,7 +924,7 @@ int forward_impl(amdp_stage* st, int aslot, int vslot, const void* X, const int3
 // with 4096 (1.3e10) 2.39 / 2.59; 768 with 3000 (2.1e10) 3.06 / 3.40; 2048 with 512 (2.6e10)
 // 4.33 / 4.41. fp32 products are several times slower: 128 wide with 128 tokens (2.5e7) 1.56 / 0.94;
 // 512 with 256 (8e8) 1.75 / 1.57; 512 with 512 (1.6e9) 2.13 / 2.02; 256 with 2048 (1.6e9) 2.40 / 2.53.
-constexpr double LEAF_INLINE_BF16 = 6e9, LEAF_INLINE_FP32 = 1e9;
+constexpr double LEAF_MIN_BF16 = 6e9, LEAF_MIN_FP32 = 1e9;
 double leaf_products(const Dims& d) {
     return (double)d.N * (4.0 * d.D * d.D + 2.0 * d.D * d.F + (d.lm ? (double)d.V * d.D / d.L : 0.0));
 }
@@ -937,7 +935,7 @@ struct Leaf {
     amdp_stage* st;
     bool ok = true;
     explicit Leaf(amdp_stage* s) : st(s) {
-        if (!st->forks()) return;
+        if (!st->overlap) return;
         hipEvent_t ev = st->next_event();
         ok = hip_ok(hipEventRecord(ev, st->stream), "hipEventRecord(fork)") &&
              hip_ok(hipStreamWaitEvent(st->side, ev, 0), "hipStreamWaitEvent(fork)");
@@ -947,7 +945,7 @@ struct Leaf {
 };
 // The main stream waits for every leaf enqueued so far.
 int join_leaves(amdp_stage* st) {
-    if (!st->forks()) return AMDP_OK;
+    if (!st->overlap) return AMDP_OK;
     hipEvent_t ev = st->next_event();
     HIP_TRY(hipEventRecord(ev, st->side));
     HIP_TRY(hipStreamWaitEvent(st->stream, ev, 0));
@@ -957,7 +955,7 @@ int join_leaves(amdp_stage* st) {
 }
 // End of a backward: remember where its leaves end instead of waiting for them.
 int mark_leaves(amdp_stage* st, int aslot) {
-    if (!st->forks()) return AMDP_OK;
+    if (!st->overlap) return AMDP_OK;
     if (!st->lazy_join) return join_leaves(st);
     HIP_TRY(hipEventRecord(st->leaves_ev[aslot], st->side));
     st->leaves_pending[aslot] = true;
@@ -1053,7 +1051,7 @@ int backward_impl(amdp_stage* st, int aslot, int vslot, const int32_t* valid, co
         };
         auto leaf_dw = [&](const void* x, const void* dy, float* dw, int n, int out, int in, bool mid_layer) -> int {
             jobs[n_jobs++] = DwJob{x, dy, dw, n, out, in};
-            if (!st->forks() || st->leaf_forks == 0 || (mid_layer && st->leaf_forks == 2)) return flush_dw(false);
+            if (!st->overlap || st->leaf_forks == 0 || (mid_layer && st->leaf_forks == 2)) return flush_dw(false);
             return AMDP_OK;
         };
 
@@ -1095,7 +1093,7 @@ int backward_impl(amdp_stage* st, int aslot, int vslot, const int32_t* valid, co
         }
         TRY(flush_dw(true));
         // the leaves of this layer read the caller's dY: remember where they end
-        if (dcur == dY && dY && st->forks()) {
+        if (dcur == dY && dY && st->overlap) {
             HIP_TRY(hipEventRecord(st->input_ev, st->side));
             dy_leaves = true;
         }
@@ -1222,8 +1220,10 @@ extern "C" int amdp_stage_create(const amdp_stage_config_t* cfg, void* workspace
     // The side stream pays while the backward's products leave compute units idle. Once
     // even the smallest weight-gradient product of a layer (D x D) fills every compute
     // unit with a 256x256 tile, concurrent kernels only share the units (measured: no
-    // gain at D = 4096, 3 % at 2048, 11 % at 1024), so it is off by default there.
-    st->overlap = (long)(st->d.D / 256) * (st->d.D / 256) < st->n_cu;
+    // gain at D = 4096, 3 % at 2048, 11 % at 1024), so it is off by default there, and it is off
+    // for a stage whose leaves are shorter than the hand-over (LEAF_MIN_BF16).
+    st->overlap = (long)(st->d.D / 256) * (st->d.D / 256) < st->n_cu &&
+                  leaf_products(st->d) > (st->d.bf ? LEAF_MIN_BF16 : LEAF_MIN_FP32);
     // Handing work to the side stream costs the host about 20 us each time (two event calls and
     // a change of the stream it enqueues on). One hand-over per product starts every leaf as
     // early as possible; two per layer cost the host half as much per backward. Measured per
@@ -1231,7 +1231,6 @@ extern "C" int amdp_stage_create(const amdp_stage_config_t* cfg, void* workspace
     // bidirectional 26.9 / 10 against 28.1 / 6.9, D = 2048 with LM head 77.0 / 6.8 against
     // 76.0 / 5.2: grouped from D = 2048 on.
     st->leaf_forks = st->d.D >= 2048 ? 2 : 0;
-    st->leaf_inline = st->d.bf ? leaf_products(st->d) <= LEAF_INLINE_BF16 : leaf_products(st->d) <= LEAF_INLINE_FP32;
     st->flash = cfg->attention == AMDP_ATTN_AUTO;
     // parameter buffers, version slots and the padding behind them start at zero
     if (device_zero(st->launch, st->base, st->w.act) != AMDP_OK) {
@@ -1644,7 +1643,6 @@ extern "C" int amdp_stage_set_option(amdp_stage_t* st, int32_t option, int32_t v
         case AMDP_OPT_LEAF_FORKS:
             if (value < 0 || value > 2) return AMDP_E_INVAL;
             st->leaf_forks = value;
-            st->leaf_inline = false;
             return AMDP_OK;
     }
     return AMDP_E_INVAL;
@@ -1681,6 +1679,5 @@ extern "C" int amdp_stage_set_overlap(amdp_stage_t* st, int32_t on) {
     if (on && !st->side) return AMDP_E_INVAL;   // the stage was created without a side stream
     TRY(join_leaves(st));                       // work still on the side stream stays ordered
     st->overlap = on != 0;
-    st->leaf_inline = false;
     return AMDP_OK;
 }

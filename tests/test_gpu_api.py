@@ -72,12 +72,12 @@ def test_profile_counts_every_launch_with_the_side_stream_on():
     w = W.TINY["gpt_tile"]
     gpu = GpuStage(w, act_slots=2, stash_slots=1)
     gpu.set_state(_theta(w))
-    assert gpu.stage.amdp_stage_get_overlap()
     x, dy = gpu.to_dev(W.make_x(w, 0), gpu.dt), gpu.to_dev(W.make_dy(w, 0), gpu.dt)
     y, dx = torch.empty_like(x), torch.empty_like(x)
     counts = []
     for overlap in (True, False):
         gpu.stage.amdp_stage_set_overlap(overlap)
+        assert gpu.stage.amdp_stage_get_overlap() == overlap
         gpu.stage.amdp_stage_profile_begin()
         gpu.stage.amdp_stage_forward(overlap, 0, x, None, y)
         gpu.stage.amdp_stage_backward(overlap, 0, dy, dx)

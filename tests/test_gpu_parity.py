@@ -268,12 +268,11 @@ def test_side_stream_on_off_bit_identical():
     dys = {m: torch.from_numpy(W.make_dy(w, m)).to("cuda:0").to(torch.bfloat16) for m in range(24)}
     finals = []
     # lazy 0: every backward ends by joining its leaves; forks: hand-overs to the side stream per layer
-    # (0 = one per product, the default at this width)
+    # (0 = one per product)
     for overlap, lazy, forks in ((True, 1, 0), (True, 0, 0), (False, 1, 0), (True, 1, 1), (True, 1, 2)):
         gpu = GpuStage(w, act_slots=12, stash_slots=3, options={OPT_LAZY_JOIN: lazy, OPT_LEAF_FORKS: forks})
         gpu.set_state(theta0)
-        assert gpu.stage.amdp_stage_get_overlap()          # narrow stage: the side stream is on by default
-        gpu.stage.amdp_stage_set_overlap(overlap)
+        gpu.stage.amdp_stage_set_overlap(overlap)           # small stage: off by default
         assert gpu.stage.amdp_stage_get_overlap() == overlap
         y = torch.empty((w.tokens, w.d_model), dtype=torch.bfloat16, device="cuda:0")
         dx = torch.empty_like(y)
@@ -321,6 +320,7 @@ def test_caller_may_overwrite_dy_right_after_backward():
     for clobber in (False, True):
         gpu = GpuStage(w)
         gpu.set_state(theta0)
+        gpu.stage.amdp_stage_set_overlap(True)              # small stage: off by default
         assert gpu.stage.amdp_stage_get_overlap()
         y, dx, dy = torch.empty_like(x), torch.empty_like(x), dy0.clone()
         gpu.stage.amdp_stage_forward(0, 0, x, None, y)
@@ -351,6 +351,7 @@ def test_fused_accumulate_bit_identical(key):
     finals = []
     for fused in (False, True):
         gpu = GpuStage(w, act_slots=w.act_slots, stash_slots=2)
+        gpu.stage.amdp_stage_set_overlap(True)      # small stage: off by default
         gpu.set_state(theta0)
         gpu.stage.amdp_stage_set_fused_accumulate(fused)
         dt = gpu.dt
@@ -409,6 +410,7 @@ def test_input_embedding_gradient_is_deterministic_and_fuses():
     res = []
     for fused in (False, False, True):
         gpu = GpuStage(w, act_slots=2, stash_slots=1)
+        gpu.stage.amdp_stage_set_overlap(True)      # small stage: off by default
         gpu.set_state(theta0)
         gpu.stage.amdp_stage_set_fused_accumulate(fused)
         tok = gpu.to_dev(W.make_tokens(w, 0))
@@ -431,6 +433,8 @@ def test_tied_embedding_gradients_are_summed_into_both_stages():
     wl = W.TINY["lmhead_tile"]
     assert wf.vocab == wl.vocab and wf.d_model == wl.d_model
     first, last = GpuStage(wf, act_slots=2, stash_slots=1), GpuStage(wl, act_slots=2, stash_slots=1)
+    first.stage.amdp_stage_set_overlap(True)        # small stages: off by default
+    last.stage.amdp_stage_set_overlap(True)
     from oracle.stage import Stage as OStage
     first.set_state(W.make_theta(wf, OStage.from_workload(wf).layout))
     last.set_state(W.make_theta(wl, OStage.from_workload(wl).layout))
@@ -472,10 +476,11 @@ def test_comparison_schedules_through_the_stage_library(name, kw):
     assert rep["ok"], worst_entries(rep)
 
 
-def test_hip_graph_replay_matches_eager():
+@pytest.mark.parametrize("overlap", [True, False])
+def test_hip_graph_replay_matches_eager(overlap):
     """Forward + backward + accumulate captured once in a HIP graph (the library
-    clears and copies with its own kernels and forks / joins its side stream
-    with events, all of which a capture records) and replayed three times with
+    clears and copies with its own kernels and, with the side stream on, forks and
+    joins it with events, all of which a capture records) and replayed three times with
     eager work and synchronisation in between must reproduce, bit for bit, the
     eager results: Y, dX, and G after one, two and three accumulations."""
     import torch
@@ -492,6 +497,7 @@ def test_hip_graph_replay_matches_eager():
 
     def fresh():
         st = amdp.Stage(cfg, device="cuda:0", stream=s)
+        st.amdp_stage_set_overlap(overlap)
         with torch.cuda.stream(s):
             st.amdp_stage_set_state(theta0)
         s.synchronize()
