@@ -459,11 +459,13 @@ int amdp_device_copy(void* dst, const void* src, size_t bytes, void* hip_stream)
  *                                    estimate says that this is faster. A value set here replaces that
  *                                    choice for weight gradients: a product too small to give every
  *                                    compute unit a 128x128 tile is split over its tokens so that a part
- *                                    contracts at least this many (at least 64; a large value: no split)
+ *                                    contracts at least this many (at least 64; a large value: no split;
+ *                                    0, the default: the library's choice again)
  *   AMDP_OPT_SPLIT_MAIN_MIN_K        the same for products of the forward / dX chain: one whose 256x256
  *                                    tiles cover at most half of the compute units runs in two halves,
  *                                    added in order together with bias and residual, when a half is at
- *                                    least this long (at least 64; a large value: no split)
+ *                                    least this long (at least 64; a large value: no split; 0, the
+ *                                    default: the library's choice again)
  *   AMDP_OPT_LEAF_FORKS              with the side stream on, how often per layer a backward hands its
  *                                    parameter-gradient work to the side stream: 0 once per product
  *                                    (default below d_model 2048: every product starts as early as it

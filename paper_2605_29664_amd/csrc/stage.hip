@@ -1633,11 +1633,11 @@ extern "C" int amdp_stage_set_option(amdp_stage_t* st, int32_t option, int32_t v
             st->lazy_join = value != 0;
             return AMDP_OK;
         case AMDP_OPT_SPLIT_K_MIN_TOKENS:
-            if (value < 64) return AMDP_E_INVAL;
+            if (value < 64 && value != 0) return AMDP_E_INVAL;
             st->splitk_min_k = value;
             return AMDP_OK;
         case AMDP_OPT_SPLIT_MAIN_MIN_K:
-            if (value < 64) return AMDP_E_INVAL;
+            if (value < 64 && value != 0) return AMDP_E_INVAL;
             st->split_main_min_k = value;
             return AMDP_OK;
         case AMDP_OPT_LEAF_FORKS:

@@ -63,3 +63,26 @@ def test_contractions_split_by_the_plan(fused):
         assert np.array_equal(sums[0], sums[1]) and np.array_equal(dxs[0], dxs[1])
         # one bf16 rounding of an activation may flip between the two orders of summation: 2^-9 of some entries
         assert rel_err(sums[0], sums[2]) < 2e-3 and rel_err(dxs[0], dxs[2]) < 4e-3
+
+
+def test_split_options_give_the_choice_back():
+    """0 takes both split options back to the library's own choice, as before either was set."""
+    import torch
+    w = W.TINY["gpt_tile64"].with_(n_layers=1, seq_len=200, microbatch=2, d_ffn=16392)
+    from oracle.stage import Stage as OStage
+    gpu = GpuStage(w, act_slots=1, stash_slots=1)
+    gpu.set_state(W.make_theta(w, OStage.from_workload(w).layout))
+    x, dy = gpu.to_dev(W.make_x(w, 0), gpu.dt), gpu.to_dev(W.make_dy(w, 0), gpu.dt)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    splits = []
+    for value in (None, 1 << 20, 0):
+        for opt in (OPT_SPLIT_K_MIN_TOKENS, OPT_SPLIT_MAIN_MIN_K):
+            if value is not None:
+                gpu.stage.amdp_stage_set_option(opt, value)
+        gpu.stage.amdp_stage_profile_begin()
+        gpu.stage.amdp_stage_forward(0, 0, x, None, y)
+        gpu.stage.amdp_stage_backward(0, 0, dy, dx)
+        gpu.stage.amdp_grad_accumulate(0)
+        splits.append({k: v["launches"] for k, v in gpu.stage.amdp_stage_profile_end().items() if k.endswith("_splitk")})
+    gpu.stage.close()
+    assert splits[0] and not splits[1] and splits[2] == splits[0]
