@@ -39,18 +39,18 @@ __device__ __forceinline__ u32x4 buffer_rsrc(const void* p, unsigned bytes) {
 constexpr unsigned BUF_OOB = 0x80000000u;      // a lane offset past the end of every descriptor used here (< 2 GiB)
 
 // 16 bytes per lane from rsrc + voff + soff to LDS: lane l's data lands at
-// lds_addr + 16 l (lds_addr uniform, it travels in M0); zeros for a lane whose
+// lds_addr + 16 l (lds_addr uniform, in M0); zeros for a lane whose
 // 16 bytes are not inside the descriptor. Written as an asm statement on
 // purpose: with the compiler's own builtin its wait-count pass puts a full
 // vmcnt(0) wait in front of every transposing LDS read that follows (it cannot
 // tell that those read another LDS slot), which serialises the loads with the
-// matrix work. The waits that are needed are written out below. M0 is a reserved
-// register: the compiler keeps no value in it across statements and sets it right
-// before each of its own uses, so it needs no restoring (saving and restoring it
-// cost 3 to 10 % of a 256x256 product's main loop in issue slots).
+// matrix work. The waits that are needed are written out below. M0 is an operand of
+// the statement, so the compiler sets it and knows its value (saving and restoring it
+// around a move inside the statement cost 3 to 10 % of a 256x256 product's main loop
+// in issue slots).
 __device__ __forceinline__ void load16_to_lds(u32x4 rsrc, unsigned voff, unsigned soff, lds_u8* lds_addr) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"((unsigned)(__UINTPTR_TYPE__)lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "{m0}"((unsigned)(__UINTPTR_TYPE__)lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
                  : "memory");
 }
 // s_barrier without the waits and fences of __syncthreads: what has to have
