@@ -444,10 +444,11 @@ int amdp_device_copy(void* dst, const void* src, size_t bytes, void* hip_stream)
 /* Kernel-selection switches for tests and measurements; none changes what is
  * computed beyond rounding order inside a product. Takes effect from the next
  * call on.
- *   AMDP_OPT_GEMM_TILE               0 = the library's choice (default); 256, 128, 64 force that
- *                                    matrix-core tile, BM*1000+BN (128064, 64128) the register-staged
- *                                    kernel with that tile where it divides the product's shape;
- *                                    -1 = generic kernel
+ *   AMDP_OPT_GEMM_TILE               0 = the library's choice (default); 256, 256128 (256 rows by 128
+ *                                    columns), 128, 64 force that matrix-core tile, 128 and 64 in the
+ *                                    form that the number of tiles asks for; 128064, 64128 the
+ *                                    register-staged kernel with that tile where it divides the
+ *                                    product's shape; -1 = generic kernel
  *   AMDP_OPT_GEMM_TRANSPOSING_READS  1 (default) m/n-contiguous operands of the register-staged kernel
  *                                    are read from LDS with the transposing read; 0 element by element
  *   AMDP_OPT_GEMM_DIRECT_TO_LDS      1 (default), 2: plain products load their tiles from global memory

@@ -453,7 +453,7 @@ DlPlan choose_dl(const amdp_stage* st, const GemmArgs& g, bool dw) {
     const size_t scratch = dw ? st->w.splitk_bytes : st->w.splitm_bytes;
     if (st->force_tile > 0) {
         const long t128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128), t64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
-        return {st->force_tile == 256 ? DL_256 : st->force_tile == 128 ? (t128 > st->n_cu ? DL_128_PAIR : DL_128)
+        return {st->force_tile == 256 ? DL_256 : st->force_tile == 256128 ? DL_256x128 : st->force_tile == 128 ? (t128 > st->n_cu ? DL_128_PAIR : DL_128)
                                                : (t64 > 2 * st->n_cu ? DL_64 : DL_64_DEEP), 1, g.K};
     }
     if (may_split && dw && st->splitk_min_k && g.M % 128 == 0 && g.N % 128 == 0) {
@@ -472,8 +472,9 @@ DlPlan choose_dl(const amdp_stage* st, const GemmArgs& g, bool dw) {
 
 template <bool A_KM, bool B_KM>
 int gemm_bf16_layout(amdp_stage* st, const GemmArgs& g) {
-    const bool square = st->force_tile == 0 || st->force_tile == 256 || st->force_tile == 128 || st->force_tile == 64;
-    if (!st->use_direct || !square || !mfma_dl_shape_ok(g, A_KM, B_KM)) return gemm_bf16_staged<A_KM, B_KM>(st, g);
+    const int t = st->force_tile;
+    const bool staged_tile = t != 0 && t != 256 && t != 256128 && t != 128 && t != 64;
+    if (!st->use_direct || staged_tile || !mfma_dl_shape_ok(g, A_KM, B_KM)) return gemm_bf16_staged<A_KM, B_KM>(st, g);
     const DlPlan p = choose_dl(st, g, A_KM);
     char name[48];
     snprintf(name, sizeof(name), "gemm_mfma%dx%d_%s%s", DL_MODEL[p.tile].bm, DL_MODEL[p.tile].bn, A_KM ? "TN" : (B_KM ? "NN" : "NT"),

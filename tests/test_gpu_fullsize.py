@@ -98,8 +98,8 @@ def test_config5_width_three_stashed_versions():
 @pytest.mark.parametrize("key", ["paper_gpt_h1600", "paper_bert_h1600"])
 def test_paper_shaped_one_layer(key):
     """Hidden size 1600 (Table 2): multiples of 64 that are not multiples of
-    128, 25 heads of 64 (fused attention) or 32 heads of 50 (unfused attention
-    on the generic kernels, heads not 16-byte aligned)."""
+    128, 25 heads of 64 or 32 heads of 50 (fused attention in its ragged form,
+    heads not 16-byte aligned)."""
     w = W.PAPER[key].with_(n_layers=1)
     print(f"\n[{key} one layer at full width] start", flush=True)
     rep = run_parity(w, threshold=1, n_minibatches=1, verbose=True,

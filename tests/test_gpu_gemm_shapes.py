@@ -1,6 +1,6 @@
 """Products whose sides are multiples of 8 but of no tile, on every tile of the
-direct-to-LDS matrix kernel, and products whose contraction the library splits by
-itself: whole small stages against the CPU oracle (tests/parity.py)."""
+direct-to-LDS matrix kernel in each of its forms, and products whose contraction the
+library splits by itself: whole small stages against the CPU oracle (tests/parity.py)."""
 import numpy as np
 import pytest
 
@@ -20,12 +20,51 @@ SHAPES = {
 }
 
 
-@pytest.mark.parametrize("tile", [0, 256, 128, 64])
+@pytest.mark.parametrize("tile", [0, 256, 256128, 128, 64])
 @pytest.mark.parametrize("shape", list(SHAPES))
 def test_sides_of_no_tile(shape, tile):
     w = W.TINY["gpt_mid"].with_(n_layers=1, depth=2, pipelines=1, stage=1, threshold=2, **SHAPES[shape])
     rep = run_parity(w, n_windows=1, verbose=False, options={OPT_GEMM_TILE: tile})
     assert rep["ok"], worst_entries(rep)
+
+
+def _product_names(w, options):
+    """Profile names of one minibatch's products."""
+    import torch
+    from oracle.stage import Stage as OStage
+    gpu = GpuStage(w, act_slots=1, stash_slots=1, options=options)
+    gpu.set_state(W.make_theta(w, OStage.from_workload(w).layout))
+    x, dy = gpu.to_dev(W.make_x(w, 0), gpu.dt), gpu.to_dev(W.make_dy(w, 0), gpu.dt)
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    gpu.stage.amdp_stage_profile_begin()
+    gpu.stage.amdp_stage_forward(0, 0, x, None, y)
+    gpu.stage.amdp_stage_backward(0, 0, dy, dx)
+    names = {k for k in gpu.stage.amdp_stage_profile_end() if k.startswith("gemm_")}
+    gpu.stage.close()
+    return names
+
+
+# More than 256 tiles of 128x128 and more than 512 of 64x64 in products of every layout (2064 x 4104, 2064 x 3096 and
+# 1032 x 4104 outputs, no side a multiple of any tile, contractions with tails of 8 and 16): there 128 and 64 take
+# their forms with two and five workgroups to a compute unit, and the smaller shapes above those with one and two
+@pytest.mark.parametrize("tile", [256, 256128, 128, 64])
+def test_many_tiles_with_odd_sides(tile):
+    w = W.TINY["gpt_mid"].with_(n_layers=1, depth=2, pipelines=1, stage=1, seq_len=1032, microbatch=2, d_model=1032, n_heads=12,
+                                d_ffn=4104)
+    rep = run_parity(w, threshold=1, n_minibatches=1, verbose=False, options={OPT_GEMM_TILE: tile})
+    assert rep["ok"], worst_entries(rep)
+    size = "256x128" if tile == 256128 else f"{tile}x{tile}"
+    assert _product_names(w, {OPT_GEMM_TILE: tile}) == {f"gemm_mfma{size}_{layout}" for layout in ("NN", "NT", "TN")}
+
+
+def test_library_choice_with_odd_sides():
+    """3 x 1000 tokens, 768 wide: the choice goes to 256x128 and 128x128 tiles, whose last rows are cut."""
+    w = W.TINY["gpt_mid"].with_(n_layers=1, depth=2, pipelines=1, stage=1, seq_len=1000, microbatch=3, d_model=768, n_heads=12,
+                                d_ffn=3072)
+    rep = run_parity(w, threshold=1, n_minibatches=1, verbose=False)
+    assert rep["ok"], worst_entries(rep)
+    names = _product_names(w, None)
+    assert any("256x128" in n for n in names) and any("128x128" in n for n in names), names
 
 
 def test_lm_head_with_odd_sides():

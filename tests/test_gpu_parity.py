@@ -23,7 +23,7 @@ def _report(name, rep):
         print("    ", d, flush=True)
 
 
-# ---- small fp32 stages: every op, ragged shapes, generic kernels -------------
+# ---- small fp32 stages: every op, ragged shapes ------------------------------
 @pytest.mark.parametrize("key", ["gpt", "bert", "lmhead"])
 @pytest.mark.parametrize("policy", [OSched.STASHED, OSched.CURRENT])
 def test_tiny_fp32(key, policy):
@@ -44,7 +44,7 @@ def test_config1_eager_and_current():
     assert rep["ok"], worst_entries(rep)
 
 
-# ---- bf16, shapes that are not tile multiples: generic kernels in bf16 -------
+# ---- bf16, shapes that are not tile multiples: ragged last tiles -------------
 @pytest.mark.parametrize("key", ["gpt_mid", "bert_mid", "lmhead_mid"])
 def test_mid_bf16_ragged(key):
     rep = run_parity(W.TINY[key], n_windows=1, verbose=False)
@@ -56,7 +56,11 @@ def test_mid_bf16_ragged(key):
 @pytest.mark.parametrize("key", ["gpt_tile", "bert_tile", "lmhead_tile"])
 @pytest.mark.parametrize("tr", [1, 0])
 def test_tile_bf16_mfma(key, tr):
-    rep = run_parity(W.TINY[key], n_windows=1, verbose=False, options={OPT_GEMM_TRANSPOSING_READS: tr})
+    """tr 1: the library's choice; 0: every product on the register-staged kernel (attention with its scores in
+    memory, so that its batched and banded products run there too) reading LDS element by element."""
+    rep = run_parity(W.TINY[key], n_windows=1, verbose=False,
+                     **({} if tr else dict(options={OPT_GEMM_TRANSPOSING_READS: 0, OPT_GEMM_DIRECT_TO_LDS: 0},
+                                           cfg_kw=dict(attention=ATTN_UNFUSED))))
     _report(f"{key}_tr{tr}", rep)
     assert rep["ok"], worst_entries(rep)
 
@@ -81,15 +85,15 @@ def test_tile_bf16_head_dim_128(key):
     assert rep["ok"], worst_entries(rep)
 
 
-@pytest.mark.parametrize("direct", [2, 1, 0])
+@pytest.mark.parametrize("direct,tr", [(1, 1), (0, 1), (0, 0)])
 @pytest.mark.parametrize("tile", [256, 128, 128064, 64128, 64])
-def test_tile_bf16_forced_tile(tile, direct):
-    """Every matrix-core tile shape on the same workload (a tile that does not
-    divide a product's shape leaves that product to the default choice), with
-    the plain products loading their tiles straight into LDS wherever the shape
-    allows (2), where the dispatch rule says so (1), and never (0)."""
+def test_tile_bf16_forced_tile(tile, direct, tr):
+    """Every matrix-core tile shape on the same workload: the plain products loading their tiles straight into LDS
+    (1; the rectangular tiles are the register-staged kernel's either way) and through the register-staged kernel
+    (0; a tile that does not divide a product's shape leaves that product to the default choice), with and without
+    the transposing LDS read."""
     rep = run_parity(W.TINY["gpt_tile"], n_windows=1, verbose=False,
-                     options={OPT_GEMM_TILE: tile, OPT_GEMM_DIRECT_TO_LDS: direct})
+                     options={OPT_GEMM_TILE: tile, OPT_GEMM_DIRECT_TO_LDS: direct, OPT_GEMM_TRANSPOSING_READS: tr})
     _report(f"gpt_tile_forced_{tile}", rep)
     assert rep["ok"], worst_entries(rep)
 
@@ -110,7 +114,7 @@ def test_tile_bf16_ragged_last_tile(key, tile):
 def test_weight_gradients_split_over_tokens(key):
     """Weight-gradient products too small to fill the GPU are split over their
     tokens into parts that are added in fixed order. At the tile test shapes
-    that needs the part size lowered to 64 tokens (default 512): the 256x256
+    that needs the part size set to 64 tokens: the 256x256
     product then runs in four parts, the wider ones in two. Checked against the
     oracle, run to run, and with the accumulation fused into the second stage."""
     import torch
@@ -145,7 +149,7 @@ def test_main_chain_products_with_split_contraction(key):
     """Products of the forward / dX chain with few 256x256 tiles and a long
     contraction run in two halves into fp32 scratch, added in order with bias and
     residual by a second kernel. At the tile test shapes that needs the minimum
-    half lowered to 64 (default 3072); the profile shows that the path ran."""
+    half set to 64; the profile shows that the path ran."""
     import torch
     w = W.TINY[key]
     rep = run_parity(w, n_windows=1, verbose=False, options={OPT_SPLIT_MAIN_MIN_K: 64})
@@ -241,10 +245,26 @@ def test_zero_lr_versions_bit_identical():
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("key", ["gpt_tile", "bert_tile"])
+# heads whose width no fused kernel takes: odd (rows at odd multiples of 2 bytes), wider than 128
+@pytest.mark.parametrize("key", ["gpt_mid", "bert_mid"])
+@pytest.mark.parametrize("heads,width", [(8, 25), (8, 3), (2, 136)])
+def test_bf16_attention_with_scores_in_memory(key, heads, width):
+    import paper_2605_29664_amd as amdp
+    w = W.TINY[key].with_(n_layers=1, d_model=heads * width, n_heads=heads, d_ffn=2 * heads * width)
+    auto, unfused = (amdp.amdp_stage_workspace_bytes(amdp.make_config(**W.stage_config_args(w, attention=a)))
+                     for a in (0, ATTN_UNFUSED))
+    assert auto == unfused                           # the probabilities are kept, as in the form that asks for it
+    rep = run_parity(w, n_windows=1, verbose=False)
+    _report(f"{key}_{heads}x{width}", rep)
+    assert rep["ok"], worst_entries(rep)
+
+
+@pytest.mark.parametrize("key", ["gpt_tile", "bert_tile", "gpt_mid", "bert_mid", "bert_dh50"])
 def test_unfused_attention_fallback(key):
     """The configuration can ask for the three-kernel attention (scores, softmax
-    and probabilities in HBM); it must meet the same tolerance as the fused one."""
+    and probabilities in HBM); it must meet the same tolerance as the fused one.
+    Tile-aligned stages run its products on the matrix cores, the others on the
+    generic kernel."""
     rep = run_parity(W.TINY[key], n_windows=1, verbose=False, cfg_kw=dict(attention=ATTN_UNFUSED))
     _report(f"{key}_unfused_attention", rep)
     assert rep["ok"], worst_entries(rep)
