@@ -71,11 +71,11 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& p, int first) {
     return out;
 }
 
-// A-operand fragment (rows = 32 consecutive columns c0.. of the tile, k = the
-// permuted 16 keys of k-step `ks` inside the 32-row group starting at row r0).
 // Nothing is moved across it by the compiler's scheduler.
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
+// A-operand fragment (rows = 32 consecutive columns c0.. of the tile, k = the
+// permuted 16 keys of k-step `ks` inside the 32-row group starting at row r0).
 template <int STRIDE>
 __device__ __forceinline__ bf16x8 frag_tr(lds_u8* tile, int r0, int ks, int c0, int lane) {
     // rows 16ks + 4h + j (h = lane / 32, j = 0..3) sit at positions 16ks + 4j + h,

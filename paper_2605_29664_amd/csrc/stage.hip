@@ -531,15 +531,15 @@ int gemm(amdp_stage* st, GemmLayout lay, GemmArgs g, long lda, long ldb) {
 // without idle lanes), a workgroup to a row for more. Wave -> workgroup in us (forward, backward): 2048
 // rows of 4096 13.2 -> 11.1, 19.2 -> 16.5; 1024 rows of 8192 17.7 -> 12.3, 26.3 -> 17.1; 512 rows of 2048
 // 7.3 -> 6.5, 8.4 -> 6.5; 4096 rows of 2048 11.2 -> 11.5, 15.0 -> 14.2; 4096 rows of 1600 10.5 -> 10.9,
-// 13.4 -> 12.5: MANY (the forward with at least LN_FWD_WAVE_ROWS rows) stays with waves for up to four.
+// 13.4 -> 12.5: the forward with at least LN_FWD_WAVE_ROWS rows stays with waves for up to four. FOUR: the
+// launch for three or four vectors a lane.
 constexpr int LN_FWD_WAVE_ROWS = 4096;
-#define LN_ROW_KERNEL(T, D, MANY, KERN, GENERIC)                                                          \
+#define LN_ROW_KERNEL(T, D, FOUR, KERN, GENERIC)                                                          \
     do {                                                                                                  \
         const int vectors_ = (D) % Vec<T>::N ? 1 << 30 : ((D) / Vec<T>::N + 63) / 64;                     \
         if (vectors_ <= 1) KERN(1, 1);                                                                    \
         else if (vectors_ <= 2) KERN(2, 1);                                                               \
-        else if (vectors_ <= 4 && (MANY)) KERN(4, 1);                                                     \
-        else if (vectors_ <= 4) KERN(1, 4);                                                               \
+        else if (vectors_ <= 4) { FOUR; }                                                                 \
         else if (vectors_ <= 8) KERN(2, 4);                                                               \
         else if (vectors_ <= 16) KERN(4, 4);                                                              \
         else GENERIC;                                                                                     \
@@ -550,7 +550,7 @@ int launch_ln_fwd(hipStream_t s, const void* x, const void* gamma, const void* b
                   int D, float eps) {
 #define LN_ARGS dim3(256), 0, s, (const T*)x, (const T*)gamma, (const T*)beta, (T*)y, stats, N, D, eps
 #define LN_FWD(NV, WPR) hipLaunchKernelGGL((ln_fwd_reg_kernel<T, NV, WPR>), row_grid(WPR == 1 ? row_blocks(N) : N), LN_ARGS)
-    LN_ROW_KERNEL(T, D, N >= LN_FWD_WAVE_ROWS, LN_FWD, hipLaunchKernelGGL(ln_fwd_kernel<T>, row_grid(row_blocks(N)), LN_ARGS));
+    LN_ROW_KERNEL(T, D, if (N >= LN_FWD_WAVE_ROWS) LN_FWD(4, 1); else LN_FWD(1, 4), LN_FWD, hipLaunchKernelGGL(ln_fwd_kernel<T>, row_grid(row_blocks(N)), LN_ARGS));
 #undef LN_FWD
 #undef LN_ARGS
     return after_launch();
@@ -561,7 +561,7 @@ int launch_ln_bwd(hipStream_t s, const void* dy, const void* x, const float* sta
                   const void* res, void* dx, int N, int D) {
 #define LN_ARGS dim3(256), 0, s, (const T*)dy, (const T*)x, stats, (const T*)gamma, (const T*)res, (T*)dx, N, D
 #define LN_BWD(NV, WPR) hipLaunchKernelGGL((ln_bwd_reg_kernel<T, NV, WPR>), row_grid(WPR == 1 ? row_blocks(N) : N), LN_ARGS)
-    LN_ROW_KERNEL(T, D, false, LN_BWD, hipLaunchKernelGGL(ln_bwd_kernel<T>, row_grid(row_blocks(N)), LN_ARGS));
+    LN_ROW_KERNEL(T, D, LN_BWD(1, 4), LN_BWD, hipLaunchKernelGGL(ln_bwd_kernel<T>, row_grid(row_blocks(N)), LN_ARGS));
 #undef LN_BWD
 #undef LN_ARGS
     return after_launch();
@@ -592,6 +592,14 @@ int launch_colsum_rows(hipStream_t s, ColSumBatch b, int accumulate) {
     return after_launch();
 }
 
+inline int device_cu_count() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    return cus;
+}
+
 // Column sums in two deterministic stages through `partial` (fp32 [chunks][width]).
 // The split of the rows: enough chunks to put ~8 blocks on every compute unit, at
 // least 16 rows each (a wave then has four rows' loads in flight), at most
@@ -608,7 +616,7 @@ inline ColSumPlan plan_column_sums(int N, int C, int vec, int n_cu, int max_chun
 // out[0..C) = column sums of dy [N, C]; with LN: out[0..C) = sum dy*xhat, out[C..2C) = sum dy
 template <class T, bool LN>
 int launch_column_sums(hipStream_t s, const void* dy, const void* x, const float* stats, float* partial, float* out,
-                       int N, int C, const ColSumPlan& p, int accumulate) {
+                       int N, int C, int max_chunks, int accumulate) {
     if (N <= COLSUM_ONE_LAUNCH_ROWS) {
         ColSumBatch b{};
         b.n = 1;
@@ -616,6 +624,7 @@ int launch_column_sums(hipStream_t s, const void* dy, const void* x, const float
         b.seg[0].dy = dy; b.seg[0].x = LN ? x : nullptr; b.seg[0].stats = stats; b.seg[0].out = out; b.seg[0].C = C;
         return launch_colsum_rows<T>(s, b, accumulate);
     }
+    const ColSumPlan p = plan_column_sums(N, C, Vec<T>::N, device_cu_count(), max_chunks);
     hipLaunchKernelGGL((colreduce_partial_kernel<T, LN>), dim3(p.col_blocks, p.chunks), dim3(256), 0, s,
                        (const T*)dy, (const T*)x, stats, partial, N, C, p.rows_per_chunk);
     TRY(after_launch());
@@ -1201,12 +1210,7 @@ extern "C" int amdp_stage_create(const amdp_stage_config_t* cfg, void* workspace
     if (workspace_bytes < st->w.total) { delete st; return AMDP_E_INVAL; }
     st->base = (char*)workspace;
     st->stream = (hipStream_t)hip_stream;
-    {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-            st->n_cu = cus;
-    }
+    st->n_cu = device_cu_count();
     st->launch = st->stream;
     st->n_vslots = cfg->stash_slots + 1;
     {
@@ -1489,13 +1493,6 @@ extern "C" int amdp_tie_embedding_grads(amdp_stage_t* first, amdp_stage_t* last)
 
 // ---- row operators of the block, callable on their own ---------------------------
 namespace {
-int device_cu_count() {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
-    return cus;
-}
 // rows x cols of `dtype`, 16-byte vectors along a row
 bool row_op_shape_ok(int32_t rows, int32_t cols, int32_t dtype) {
     if (dtype != AMDP_FP32 && dtype != AMDP_BF16) return false;
@@ -1508,12 +1505,11 @@ constexpr int COLSUM_MAX_CHUNKS = 256;
 int column_sums_impl(const void* dy, const void* x, const float* stats, float* out, int32_t rows, int32_t cols,
                      int32_t dtype, float* partial, int max_chunks, hipStream_t s) {
     const bool ln = x != nullptr;
-    const ColSumPlan p = plan_column_sums(rows, cols, dtype == AMDP_BF16 ? 8 : 4, device_cu_count(), max_chunks);
     if (dtype == AMDP_BF16)
-        return ln ? launch_column_sums<bf16, true>(s, dy, x, stats, partial, out, rows, cols, p, 0)
-                  : launch_column_sums<bf16, false>(s, dy, nullptr, nullptr, partial, out, rows, cols, p, 0);
-    return ln ? launch_column_sums<float, true>(s, dy, x, stats, partial, out, rows, cols, p, 0)
-              : launch_column_sums<float, false>(s, dy, nullptr, nullptr, partial, out, rows, cols, p, 0);
+        return ln ? launch_column_sums<bf16, true>(s, dy, x, stats, partial, out, rows, cols, max_chunks, 0)
+                  : launch_column_sums<bf16, false>(s, dy, nullptr, nullptr, partial, out, rows, cols, max_chunks, 0);
+    return ln ? launch_column_sums<float, true>(s, dy, x, stats, partial, out, rows, cols, max_chunks, 0)
+              : launch_column_sums<float, false>(s, dy, nullptr, nullptr, partial, out, rows, cols, max_chunks, 0);
 }
 }  // namespace
 
