@@ -98,6 +98,9 @@ def build(verbose=False):
     src = [os.path.join(HERE, "csrc", "stage.hip"), os.path.join(HERE, "csrc", "schedule.cpp")]
     cmd = ["hipcc", "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # Main loops start at a 64-byte boundary: left to chance, an edit elsewhere in a kernel moves its loop and
+           # with it the products' time by up to 2.5 % (128x128 NN tile of a 1600-wide stage: 88.3 us at offset 24, 85.7 at 0).
+           "-falign-loops=64",
            "-Wno-pass-failed", "-I" + os.path.join(ROOT, "include"), "-o", lib_path()] + src
     res = subprocess.run(cmd, capture_output=True, text=True)
     if verbose or res.returncode:
