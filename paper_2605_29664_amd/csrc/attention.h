@@ -35,9 +35,9 @@
 // kernels' accumulators start at -lse and -delta instead of zero, which leaves two vector
 // instructions per score besides the exponential and the packing. Kernel times without
 // other work, before -> now (forward, dQ, dK/dV in us): 16 heads of 64, 4 x 1024 tokens,
-// causal 26.0 / 30.4 / 38.7 -> 25.5 / 28.8 / 34.7; 32 heads of 64, 2 x 2048, causal
-// 59.9 / 78.5 / 102 -> 57.4 / 73.1 / 91.6; 32 heads of 128, 2048, causal 65.9 / 95.5 / 144
-// -> 62.4 / 91.4 / 126. With the exponentials taken out the second case takes 43 / 60 / 72,
+// causal 26.2 / 30.2 / 38.8 -> 26.4 / 29.0 / 34.2; 32 heads of 64, 2 x 2048, causal
+// 59.4 / 78.6 / 102 -> 58.7 / 75.0 / 93.8; 32 heads of 128, 2048, causal 66.8 / 96.5 / 146
+// -> 63.5 / 93.3 / 128. With the exponentials taken out the second case takes 43 / 60 / 72,
 // with the tile loads taken out 52 / 68 / 87.
 #pragma once
 #include "common.h"
