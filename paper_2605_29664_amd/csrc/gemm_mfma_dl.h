@@ -466,7 +466,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_mfma_dl_kernel(GemmArgs g
 }
 
 // True when the problem satisfies every assumption of gemm_mfma_dl_kernel (any tile):
-// whole 16-byte vectors along every row, and every descriptor below 2 GiB (rows below 8 MiB).
+// whole 16-byte vectors along every row, and every descriptor below 2 GiB (rows of a k-contiguous
+// operand below 8 MiB, of an m/n-contiguous one below 32 MiB).
 inline bool mfma_dl_shape_ok(const GemmArgs& g, bool a_km, bool b_km) {
     GemmArgs t = g;
     if (g.M % 8 || g.N % 8 || g.K % 8 || g.M <= 0 || g.N <= 0 || g.K <= 0 || g.batch != 1 || g.causal) return false;
@@ -476,7 +477,7 @@ inline bool mfma_dl_shape_ok(const GemmArgs& g, bool a_km, bool b_km) {
     // elements that one descriptor covers: a k-tile of an m/n-contiguous operand, a tile's rows of a k-contiguous one
     const long ea = a_km ? MF_BK * lda : 256 * lda + g.K, eb = b_km ? MF_BK * ldb : 256 * ldb + g.K;
     constexpr long LIM = (1L << 30) - 4096 * 64;      // 2 GiB less the scalar offset's overshoot
-    return ea < LIM && eb < LIM && lda < (1 << 22) && ldb < (1 << 22);
+    return ea < LIM && eb < LIM;
 }
 
 // parts > 1: split contraction, fp32 parts at C + z * g.c_bo; k_part a multiple of MF_BK with

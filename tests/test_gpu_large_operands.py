@@ -56,3 +56,35 @@ def test_weight_gradients_over_2_gib_operands(tile):
         assert rel_err(got[tile][name], got[-1][name]) < 4e-3, name
     assert all(np.isfinite(v).all() for v in got[tile].values())
     stage.close()
+
+
+def test_vocabulary_gradient_with_rows_over_8_mib():
+    """The logits of 4.2 M words: rows of 8.4 MB, of which the gradient of the vocabulary projection contracts 64 at a
+    time. 72 columns divide into no tile, so no other matrix kernel takes it; agrees with the generic kernel's."""
+    _need(30)
+    seq, batch, d, f, vocab = 64, 2, 72, 72, 4_200_001
+    cfg = amdp.make_config(amdp.BLOCK_GPT, 1, d, 1, f, seq, batch, amdp.BF16, has_lm_head=True, vocab=vocab, act_slots=1, stash_slots=1)
+    a, b = next((off, off + r * c) for name, off, r, c in amdp.amdp_stage_param_layout(cfg) if name == "embed")
+    g = torch.Generator(device="cuda:0").manual_seed(6)
+    stage = amdp.Stage(cfg, device="cuda:0")
+    theta = 0.02 * torch.randn(stage.n_params, generator=g, device="cuda:0")
+    stage.amdp_stage_set_state(theta)
+    x = torch.randn((seq * batch, d), generator=g, device="cuda:0").bfloat16()
+    targets = torch.randint(0, vocab, (seq * batch,), generator=g, device="cuda:0", dtype=torch.int32)
+    loss = torch.empty(1, dtype=torch.float32, device="cuda:0")
+    got, names = [], []
+    for opt in (-1, 0):
+        stage.amdp_stage_set_option(amdp.OPT_GEMM_TILE, 0)
+        stage.amdp_stage_forward(0, 0, x, targets, loss)
+        stage.amdp_stage_set_option(amdp.OPT_GEMM_TILE, opt)
+        stage.amdp_stage_profile_begin()
+        stage.amdp_stage_backward(0, 0, None, None)
+        names.append([k for k in stage.amdp_stage_profile_end() if k.endswith("_TN")])
+        grad = torch.empty(stage.n_params, dtype=torch.float32, device="cuda:0")
+        stage.amdp_stage_get_staged_grad(grad)
+        stage.amdp_grad_accumulate(0)
+        got.append(grad[a:b].cpu().numpy())
+    assert names[0] == ["gemm_generic_TN"] and "gemm_generic_TN" not in names[1], names
+    assert np.isfinite(got[1]).all()
+    assert rel_err(got[1], got[0]) < 1e-6      # 128 fp32 additions of the same products in another order
+    stage.close()
